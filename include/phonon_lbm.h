@@ -322,8 +322,13 @@ int lbm_set_wall_flux(lbm_handle h, int32_t inst, int32_t wall, double q0);
  * lbm_max_step_fusion gives the kind's most).  Default
  * for a new handle: that most when its instances hold at least 1024 strips of
  * the fused kernel in all (64 - 2 k columns by 32 rows each, k the most), so
- * that a fused launch fills the chip, else 1.  The per-instance schedule
- * always issues single steps.  Drops captured graphs.  Errors: EINVAL (steps
+ * that a fused launch fills the chip, else 1.  A new handle of up to 4.5
+ * million nodes (16-bit storage: where the default is 1, or with
+ * LBM_FLAG_ROUND_EVERY_STEP) advances several steps per launch in kernels that
+ * hold the lattices on the chip, every step rounded as a stored one is: the
+ * same bits as single steps, whatever this setting's default says.  Calling
+ * this function or lbm_set_launch_shape selects the launches they describe
+ * instead.  The per-instance schedule always issues single steps.  Drops captured graphs.  Errors: EINVAL (steps
  * < 1 or more than the handle's most). */
 int lbm_set_step_fusion(lbm_handle h, int32_t steps);
 
@@ -362,7 +367,8 @@ int32_t lbm_get_streams(lbm_handle h);
 /* Kernel launch shape: nodes per thread along x (1, 2 or 4), threads per
  * block along x (a multiple of 64, <= 512) and rows per block, with
  * block_x * block_y <= 512; xcd_remap != 0 maps consecutive tiles to the same
- * XCD.  Applies to later steps; invalidates captured graphs.  Errors: EINVAL. */
+ * XCD.  Applies to later steps, which are then issued in this shape (or fused,
+ * lbm_set_step_fusion); invalidates captured graphs.  Errors: EINVAL. */
 typedef struct {
     int32_t vec;
     int32_t block_x;
@@ -376,7 +382,9 @@ int lbm_get_launch_shape(lbm_handle h, lbm_launch_shape* shape);
 /* Time every candidate launch shape on this handle's own instances and keep
  * the fastest, then time fused launches of every number of steps up to the
  * storage kind's most against it and set the steps per launch
- * (lbm_set_step_fusion) to the fastest.  Must be called after
+ * (lbm_set_step_fusion) to the fastest; the kernels that hold small lattices
+ * on the chip are timed too and kept where they are faster (16-bit storage:
+ * than single steps).  Must be called after
  * lbm_create and before lbm_init (it runs steps on scratch contents); each
  * candidate is timed over `steps` steps (0 = 20) with HIP events.  If the environment variable LBM_AUTOTUNE_CACHE
  * names a file, a result for the same device, storage and instance shapes is

@@ -51,6 +51,11 @@ struct alignas(64) InstDesc {
     int32_t p_ntiles;       // fused kernel: tiles of this instance
     int32_t p_group_begin;  // fused kernel: first reduction group (kGroup of its tiles each)
     int32_t p_ngroups;      // fused kernel: reduction groups of this instance
+    int32_t b_tiles_x;      // block kernels: tiles along x
+    int32_t b_tile_begin;   // block kernels: first global tile of this instance
+    int32_t b_ntiles;       // block kernels: tiles of this instance
+    int32_t b_group_begin;  // block kernels: first reduction group (kGroup of its tiles each)
+    int32_t b_ngroups;      // block kernels: reduction groups of this instance
     int64_t row;            // elements between rows
     int64_t plane;          // elements between direction runs
     int64_t chunk;          // elements between 64-node chunks (0: planes layout)
@@ -184,6 +189,46 @@ struct StepArgs {
     int32_t sr;                 // 1: round stores stochastically (nodes per lane must be 1)
 };
 
+// How the block kernels (lbm_block.h) hold a handle's lattices on the chip:
+//   kBlockTiles: windows of 64 columns by waves * rows rows (rows per wavefront,
+//                in registers) with a halo on each side;
+//   kBlockPatch: windows of wx by wy nodes, one per thread, in LDS, with a halo;
+//   kBlockWhole: each whole lattice in one block's LDS, `rows` nodes per thread.
+// A launch takes at most `halo` steps (kBlockWhole: any number).
+enum BlockKind { kBlockNone = 0, kBlockTiles = 1, kBlockWhole = 2, kBlockPatch = 3 };
+struct BlockPlan {
+    int kind = kBlockNone;
+    int rows = 0;        // tiles: rows per wavefront (3 or 4); whole: nodes per thread (1 or 2)
+    int waves = 0;       // wavefronts per block (<= 16)
+    int halo = 0;        // halo nodes = most steps per launch
+    int wx = 0, wy = 0;  // patch: window
+    int win_x() const { return kind == kBlockPatch ? wx : 64; }
+    int win_y() const { return kind == kBlockPatch ? wy : waves * rows; }
+    int out_x() const { return win_x() - 2 * halo; }
+    int out_y() const { return win_y() - 2 * halo; }
+};
+
+// Most nodes of a handle (all instances) that runs in the block kernels, and
+// up to which their plan comes from the cost model (see block_plan).
+constexpr int64_t kBlockNodes = 4500000;
+constexpr int64_t kBlockModelNodes = 400000;
+// Most steps of one launch of a whole lattice.
+constexpr int kWholeSteps = 512;
+
+struct BlockArgs {
+    StepArgs s;          // tile_inst / tile_base / ntiles index the block tile table
+    void* prev;          // also store the state after all steps but the last here (or null)
+    int32_t steps;       // steps of this launch
+    int32_t halo, waves; // of the plan
+    int32_t win_x, win_y;   // of the plan (patch)
+};
+
+// `steps` time steps in one launch of the block kernels, ending plain or on
+// the check step (kEndCheck, as launch_fused; launch_finalize with fused = 2).
+// The same bits as that many single steps.
+hipError_t launch_block(int storage, const BlockPlan& p, const Shape& sh, const BlockArgs& b, int end,
+                        hipStream_t st);
+
 // Host-side launchers defined in lbm_device.hip; they return hipError_t.
 // snap_stride: nodes of the whole handle (the snapshot holds dT, qx, qy planes).
 hipError_t launch_step(int storage, const Shape& sh, int mode, const StepArgs& a,
@@ -226,9 +271,9 @@ hipError_t launch_init(int storage, const InstDesc* d_desc, const RefState* d_re
 // (kPartials doubles per instance), in two fixed-order stages: groups of
 // kGroup tile records (group_inst: group -> instance; groups g0 .. g0 +
 // ngroups - 1) into gpart, then one block per instance (i0 .. i0 + ninst - 1)
-// over its groups.  fused != 0: the
-// records are per fused-kernel tile (InstDesc p_* fields), else per
-// single-step tile.  The second stage copies each instance's reference state
+// over its groups (alone, over the tile records, where every instance holds
+// one group).  fused: the records are per single-step tile (0), fused-kernel
+// tile (1, InstDesc p_* fields) or block-kernel tile (2, b_* fields).  The second stage copies each instance's reference state
 // to d_ref_prev and then moves an adaptive instance's reference flux to its
 // mean heat flux.
 hipError_t launch_finalize(const InstDesc* d_desc, const int32_t* group_inst, int g0, int ngroups, RefState* d_ref,

@@ -238,6 +238,113 @@ int64_t fused_tiles_x(const lbm_instance& in, int storage) {
     return (in.nx + fused_width(storage) - 1) / fused_width(storage);
 }
 
+// Block-kernel tiles along x and y of one instance.
+int64_t block_tiles_x(const lbm_instance& in, const BlockPlan& p) {
+    return p.kind != kBlockWhole ? (in.nx + p.out_x() - 1) / p.out_x() : 1;
+}
+int64_t block_tiles_y(const lbm_instance& in, const BlockPlan& p) {
+    return p.kind != kBlockWhole ? (in.ny + p.out_y() - 1) / p.out_y() : 1;
+}
+
+// Expected time of one step in the block kernels under plan p, in
+// microseconds: launch and load latency, the window's traffic, and the slowest
+// compute unit's steps, shared over the `halo` steps of a launch.  Constants
+// fitted to MI355X timings of FP32 lattices; the plan it picks is within 10%
+// of the fastest of 60 tried (us per step, picked / fastest / single-step
+// launches): 20 x 20 0.31 / 0.31 / 3.4, 401 x 3 0.69 / 0.65 / 3.5, 128 x 64
+// 0.75 / 0.69 / 3.5, 201^2 1.14 / 1.07 / 3.6, 401 x 301 1.48 / 1.46 / 4.1,
+// 512^2 1.97 / 1.88 / 4.9, 1024 x 256 1.97 / 1.94 / 4.9.
+double block_cost(const std::vector<lbm_instance>& v, const BlockPlan& p, int storage) {
+    const double cus = 256.0;
+    double blocks = 0.0, out_nodes = 0.0;
+    for (auto& in : v) {
+        blocks += (double)(block_tiles_x(in, p) * block_tiles_y(in, p));
+        out_nodes += (double)in.nx * in.ny;
+    }
+    const double waves = p.waves / 4.0;                         // per SIMD and block
+    if (p.kind == kBlockWhole) {
+        // 64 KB of LDS per node of a thread: two blocks or one per CU
+        const double rounds = std::ceil(blocks / (cus * (p.rows == 1 ? 2 : 1)));
+        return rounds * std::max(0.25, 0.11 * waves * p.rows) + 3.5 / 100.0;
+    }
+    const int per_cu = p.kind == kBlockPatch ? std::min(2, 32 / p.waves) : (p.rows == 3 ? 32 : 28) / p.waves;
+    const double held = std::max(1.0, std::min((double)per_cu, std::ceil(blocks / cus)));
+    const double rounds = blocks / (cus * held);
+    double step;
+    if (p.kind == kBlockPatch) {
+        step = std::max(0.4, 0.125 * waves * held);
+    } else {
+        const double active = (double)(p.out_y() + p.halo - 1) / (p.waves * p.rows);   // rows still needed, mean
+        step = 0.3 + 0.09 * waves * held * p.rows * active;
+    }
+    const double node_bytes = is_split(storage) ? 20.0 : 8.0 * esize_of(storage);
+    const double traffic = node_bytes * (blocks * p.win_x() * p.win_y() + out_nodes) / 6.0e6;
+    // a second round's loads overlap the first round's steps in part
+    return (3.4 + p.halo * step * std::max(1.0, rounds) + traffic * (rounds > 1.0 ? 0.6 : 1.0)) / p.halo;
+}
+
+// The block kernels' plan for a handle's lattices (kBlockNone: too large for
+// them).  Up to kBlockModelNodes the cheapest by block_cost; above, where many
+// rounds of blocks overlap each other's loads, steps and stores, one tile that
+// is within 2% of the best of 40 tried there (FP32 us per step, this tile /
+// best tile / marching kernel at seven steps: 999 x 777 3.79 / 3.79 / 12.0,
+// 1500 x 1100 6.95 / 6.95 / 13.3, 2048^2 15.7 / 15.7 / 17.8, 2400^2 22.6 /
+// 22.2 / 22.1: kBlockNodes lies between the last two).
+BlockPlan block_plan(const std::vector<lbm_instance>& v, int storage) {
+    int64_t most = 0, nodes = 0;
+    for (auto& in : v) {
+        most = std::max<int64_t>(most, (int64_t)in.nx * in.ny);
+        nodes += (int64_t)in.nx * in.ny;
+    }
+    BlockPlan best;
+    if (nodes > kBlockNodes) return best;
+    if (nodes > kBlockModelNodes) {
+        best.kind = kBlockTiles;
+        best.rows = 4;
+        best.waves = 12;
+        best.halo = 7;
+        return best;
+    }
+    double cost = 1e300;
+    auto consider = [&](const BlockPlan& p) {
+        const double c = block_cost(v, p, storage);
+        if (c < cost) {
+            cost = c;
+            best = p;
+        }
+    };
+    if (most <= 2048) {
+        BlockPlan p;
+        p.kind = kBlockWhole;
+        p.rows = most <= 1024 ? 1 : 2;
+        p.waves = (int)((most + 64 * p.rows - 1) / (64 * p.rows));
+        consider(p);
+    }
+    static const int windows[4][2] = {{32, 32}, {28, 28}, {32, 24}, {24, 24}};
+    for (auto& w : windows)
+        for (int halo = 6; 2 * halo + 6 <= w[1]; ++halo) {
+            BlockPlan p;
+            p.kind = kBlockPatch;
+            p.rows = 1;
+            p.wx = w[0];
+            p.wy = w[1];
+            p.waves = (w[0] * w[1] + 63) / 64;
+            p.halo = halo;
+            consider(p);
+        }
+    for (int rows = 3; rows <= 4; ++rows)
+        for (int waves = 8; waves <= 16; waves += 2)
+            for (int halo = 5; halo <= 10 && waves * rows - 2 * halo >= 8; ++halo) {
+                BlockPlan p;
+                p.kind = kBlockTiles;
+                p.rows = rows;
+                p.waves = waves;
+                p.halo = halo;
+                consider(p);
+            }
+    return best;
+}
+
 // Worst-case count of first-stage reduction groups (per instance, kGroup
 // tiles each).
 int64_t max_groups(const std::vector<lbm_instance>& v) {
@@ -251,8 +358,9 @@ struct Layout {
     size_t off_buf[3] = {0, 0, 0};   // ping-pong pair, and the readout buffer (see replay_tail)
     size_t off_snap = 0, off_part = 0, off_res = 0, off_mpart = 0, off_mres = 0, off_desc = 0,
            off_desc_prev = 0, off_ref = 0, off_ref_prev = 0, off_tiles = 0, off_ptiles = 0, off_groups = 0,
-           off_pgroups = 0, off_gpart = 0, off_ctr = 0, total = 0;
-    int64_t nodes = 0, tiles_max = 0, mparts_max = 0, groups_max = 0, ptiles = 0, pgroups = 0;
+           off_pgroups = 0, off_btiles = 0, off_bgroups = 0, off_gpart = 0, off_ctr = 0, total = 0;
+    int64_t nodes = 0, tiles_max = 0, mparts_max = 0, groups_max = 0, ptiles = 0, pgroups = 0, btiles = 0,
+            bgroups = 0;
 };
 
 // Fused launches round every step: FP32 storage, or LBM_FLAG_ROUND_EVERY_STEP.
@@ -281,11 +389,18 @@ Layout layout_of(const std::vector<lbm_instance>& v, int storage, int check, int
         L.ptiles += pt;
         L.pgroups += (pt + kGroup - 1) / kGroup;
     }
-    // check-step records: per single-step tile or per fused-kernel tile
-    const int64_t records = std::max(L.tiles_max, L.ptiles);
+    const BlockPlan bp = block_plan(v, storage);
+    if (bp.kind != kBlockNone)
+        for (auto& in : v) {
+            const int64_t bt = block_tiles_x(in, bp) * block_tiles_y(in, bp);
+            L.btiles += bt;
+            L.bgroups += (bt + kGroup - 1) / kGroup;
+        }
+    // check-step records: per single-step, fused-kernel or block-kernel tile
+    const int64_t records = std::max({L.tiles_max, L.ptiles, L.btiles});
     // the same scratch serves the first stage of every check reduction and of
     // lbm_totals' reduction
-    const int64_t gscratch = std::max({L.groups_max, L.pgroups, (L.mparts_max + kGroup - 1) / kGroup});
+    const int64_t gscratch = std::max({L.groups_max, L.pgroups, L.bgroups, (L.mparts_max + kGroup - 1) / kGroup});
     size_t o = 0;
     L.off_buf[0] = o; o += L.buf_bytes;
     L.off_buf[1] = o; o += L.buf_bytes;
@@ -303,6 +418,8 @@ Layout layout_of(const std::vector<lbm_instance>& v, int storage, int check, int
     L.off_ptiles = o; o += align_up((size_t)L.ptiles * sizeof(int32_t), kAlign);
     L.off_groups = o; o += align_up((size_t)L.groups_max * sizeof(int32_t), kAlign);
     L.off_pgroups = o; o += align_up((size_t)L.pgroups * sizeof(int32_t), kAlign);
+    L.off_btiles = o; o += align_up((size_t)L.btiles * sizeof(int32_t), kAlign);
+    L.off_bgroups = o; o += align_up((size_t)L.bgroups * sizeof(int32_t), kAlign);
     L.off_gpart = o; o += align_up((size_t)gscratch * kPartials * sizeof(DD), kAlign);
     L.off_ctr = o; o += kAlign;                 // 32-bit step counters: ping-pong pair and the readout's
     L.total = o;
@@ -336,12 +453,17 @@ struct lbm_ctx {
     std::vector<int32_t> ptile_inst;   // fused kernel: tile -> instance
     std::vector<int32_t> pgroup_inst;  // fused kernel: reduction group -> instance
     int64_t npgroups = 0;
+    BlockPlan bplan;                   // block kernels (kBlockNone: not for these instances)
+    bool block_on = false;             // single steps run in the block kernels (see plan_block)
+    std::vector<int32_t> btile_inst;   // block kernels: tile -> instance
+    std::vector<int32_t> bgroup_inst;  // block kernels: reduction group -> instance
     // The instances one launch covers: all of them, or one of the parts that
     // the batched schedule issues on streams of their own (lbm_set_streams).
     struct Span {
         int i0 = 0, ni = 0;                            // instances
         int32_t t0 = 0, nt = 0, g0 = 0, ng = 0;        // single-step tiles and reduction groups
         int32_t pt0 = 0, pnt = 0, pg0 = 0, png = 0;    // fused-kernel tiles and reduction groups
+        int32_t bt0 = 0, bnt = 0, bg0 = 0, bng = 0;    // block-kernel tiles and reduction groups
         int ctr = 0;                                   // its step-counter pair: d_ctr()[ctr], [ctr + 1]
     };
     static constexpr int kMaxParts = 2;
@@ -373,6 +495,8 @@ struct lbm_ctx {
         int src = 0;           // buffer that launch read
         int apply_shift = 0;   // its first step applied the pending reference shift
         int checked = 0;       // it ended on a check step (the reference moved after it)
+        int kept = 0;          // a block-kernel launch that also stored the state of step n - 1
+                               // in the readout buffer: nothing to replay
     } tail, graph_tail;
     int graph_tail_flip = 0;           // launches of a captured chunk before its last one, mod 2
     bool replayed = false;             // the readout buffer holds the replayed state
@@ -406,6 +530,8 @@ struct lbm_ctx {
     const InstDesc* d_desc_last() const { return desc_saved ? d_desc_prev() : d_desc(); }
     int32_t* d_tiles() const { return reinterpret_cast<int32_t*>(base + L.off_tiles); }
     int32_t* d_ptiles() const { return reinterpret_cast<int32_t*>(base + L.off_ptiles); }
+    int32_t* d_btiles() const { return reinterpret_cast<int32_t*>(base + L.off_btiles); }
+    int32_t* d_bgroups() const { return reinterpret_cast<int32_t*>(base + L.off_bgroups); }
     int32_t* d_groups() const { return reinterpret_cast<int32_t*>(base + L.off_groups); }
     DD* d_gpart() const { return reinterpret_cast<DD*>(base + L.off_gpart); }
     double* d_snap() const { return K ? reinterpret_cast<double*>(base + L.off_snap) : nullptr; }
@@ -455,6 +581,8 @@ static void build_tiles(lbm_ctx* h) {
     h->ptile_inst.clear();
     h->pgroup_inst.clear();
     h->npgroups = 0;
+    h->btile_inst.clear();
+    h->bgroup_inst.clear();
     for (size_t k = 0; k < h->inst.size(); ++k) {
         InstDesc& d = h->desc[k];
         const int tw = s.tile_w();
@@ -476,6 +604,14 @@ static void build_tiles(lbm_ctx* h) {
         d.p_ngroups = (d.p_ntiles + kGroup - 1) / kGroup;
         h->npgroups += d.p_ngroups;
         h->pgroup_inst.insert(h->pgroup_inst.end(), (size_t)d.p_ngroups, (int32_t)k);
+        if (h->bplan.kind == kBlockNone) continue;
+        d.b_tiles_x = (int32_t)block_tiles_x(h->inst[k], h->bplan);
+        d.b_tile_begin = (int32_t)h->btile_inst.size();
+        d.b_ntiles = d.b_tiles_x * (int32_t)block_tiles_y(h->inst[k], h->bplan);
+        h->btile_inst.insert(h->btile_inst.end(), (size_t)d.b_ntiles, (int32_t)k);
+        d.b_group_begin = (int32_t)h->bgroup_inst.size();
+        d.b_ngroups = (d.b_ntiles + kGroup - 1) / kGroup;
+        h->bgroup_inst.insert(h->bgroup_inst.end(), (size_t)d.b_ngroups, (int32_t)k);
     }
     make_parts(h);
 }
@@ -496,6 +632,10 @@ static lbm_ctx::Span span_of(const lbm_ctx* h, int i0, int i1, int ctr) {
     sp.pnt = b.p_tile_begin + b.p_ntiles - a.p_tile_begin;
     sp.pg0 = a.p_group_begin;
     sp.png = b.p_group_begin + b.p_ngroups - a.p_group_begin;
+    sp.bt0 = a.b_tile_begin;
+    sp.bnt = b.b_tile_begin + b.b_ntiles - a.b_tile_begin;
+    sp.bg0 = a.b_group_begin;
+    sp.bng = b.b_group_begin + b.b_ngroups - a.b_group_begin;
     return sp;
 }
 
@@ -551,6 +691,12 @@ static int upload_tables(lbm_ctx* h) {
                               hipMemcpyHostToDevice, h->stream));
     HIPCALL(h, hipMemcpyAsync(h->d_pgroups(), h->pgroup_inst.data(), h->pgroup_inst.size() * sizeof(int32_t),
                               hipMemcpyHostToDevice, h->stream));
+    if (!h->btile_inst.empty()) {
+        HIPCALL(h, hipMemcpyAsync(h->d_btiles(), h->btile_inst.data(), h->btile_inst.size() * sizeof(int32_t),
+                                  hipMemcpyHostToDevice, h->stream));
+        HIPCALL(h, hipMemcpyAsync(h->d_bgroups(), h->bgroup_inst.data(), h->bgroup_inst.size() * sizeof(int32_t),
+                                  hipMemcpyHostToDevice, h->stream));
+    }
     HIPCALL(h, hipStreamSynchronize(h->stream));
     return LBM_OK;
 }
@@ -786,6 +932,7 @@ int lbm_create(const lbm_config* cfg, lbm_handle* out) {
     h->shape.by = 1;
     h->shape.xcd = 1;
     h->shape.nt = 0;
+    h->bplan = block_plan(v, h->storage);
     build_tiles(h);
     // steps per launch: the kind's most when the instances hold enough strips
     // of the fused kernel to fill the chip, else single steps.  Measured on
@@ -794,6 +941,9 @@ int lbm_create(const lbm_config* cfg, lbm_handle* out) {
     // 8192^2 741 / 213: a fused launch takes about one strip's marching time
     // however few strips there are.
     h->fuse = (int64_t)h->ptile_inst.size() >= kFuseMinStrips ? h->fuse_cap() : 1;
+    // steps in the block kernels (the same bits as single steps) where their
+    // plan fits, unless fused launches keep 16-bit states in FP32
+    h->block_on = h->bplan.kind != kBlockNone && (h->fuse == 1 || h->every_step);
     default_costs(h->storage, h->every_step, h->cost_plain, h->cost_check);
     e = hipStreamCreateWithFlags(&h->capture_stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
@@ -1117,6 +1267,67 @@ static int issue_fused(lbm_ctx* h, int64_t m, int nsteps, int end, int src_k, hi
     return LBM_OK;
 }
 
+// Steps the block-kernel launch that starts at step m covers, in a sequence
+// of steps that ends at step `last`; 1: a single-step launch.  The steps up to
+// the next check step (or `last`) are shared out evenly over the fewest
+// launches, so that the one that reaches the check step has at least two (it
+// forms the residual against the step before).  A call's last step runs single
+// where it is the snapshot step before a check step, and so does the lone
+// check step that then starts the next call.
+static int plan_block(const lbm_ctx* h, int64_t m, int64_t last, int* end) {
+    *end = kEndPlain;
+    int64_t seg = last;
+    bool to_check = false;
+    if (h->K) {
+        const int64_t c = (m + h->K - 1) / h->K * h->K;     // first check step >= m
+        if (c <= seg) {
+            seg = c;
+            to_check = true;
+        }
+    }
+    int64_t r = seg - m + 1;
+    if (!to_check && mode_of(h, seg) == kSnap) --r;
+    if (r < 2) return 1;
+    const int64_t most = h->bplan.kind == kBlockWhole ? kWholeSteps : h->bplan.halo;
+    const int64_t n = (r + most - 1) / most;
+    const int k = (int)((r + n - 1) / n);
+    if (k == r && to_check) *end = kEndCheck;
+    return k;
+}
+
+// Issue k steps from step m in the block kernels; keep: also store the state
+// after all but the last of them in the readout buffer.
+static int issue_block(lbm_ctx* h, int64_t m, int k, int end, int src_k, bool keep, hipStream_t st,
+                       const lbm_ctx::Span& sp) {
+    BlockArgs b;
+    StepArgs& a = b.s;
+    a.desc = h->d_desc();
+    a.tile_inst = h->d_btiles();
+    a.src = h->buf(src_k);
+    a.dst = h->buf(1 - src_k);
+    a.snap = nullptr;
+    a.partials = h->d_part();
+    a.ctr_in = h->d_ctr() + sp.ctr + src_k;
+    a.ctr_out = h->d_ctr() + sp.ctr + (1 - src_k);
+    a.seed = h->seed;
+    a.sr = h->sr;
+    a.ref = h->d_ref();
+    a.apply_shift = (h->K > 0 && (m - 1) % h->K == 0) ? 1 : 0;
+    a.tile_base = sp.bt0;
+    a.ntiles = sp.bnt;
+    b.prev = keep ? h->buf(lbm_ctx::kReadout) : nullptr;
+    b.steps = k;
+    b.halo = h->bplan.halo;
+    b.waves = h->bplan.waves;
+    b.win_x = h->bplan.win_x();
+    b.win_y = h->bplan.win_y();
+    HIPCALL(h, launch_block(h->storage, h->bplan, h->shape, b, end, st));
+    if (end == kEndCheck)
+        HIPCALL(h, launch_finalize(h->d_desc(), h->d_bgroups(), sp.bg0, sp.bng, h->d_ref(), h->d_ref_prev(), sp.i0,
+                                   sp.ni, h->d_part(), h->d_gpart(), h->d_res(), 2, st));
+    return LBM_OK;
+}
+
 // Stream `side` (the second part's) waits for everything issued on `main`
 // so far, its step counters starting from the handle's; join: `main` waits
 // for everything issued on `side`.  The events and `side` are created at first
@@ -1161,19 +1372,23 @@ static int capture(lbm_ctx* h, int par) {
     int tail_flip = 0;
     for (int s = 1; s <= C && rc == LBM_OK;) {
         int end = kEndPlain;
-        const int k = plan_launch(h, s, C, &end);
+        const bool block = h->block_on;
+        const int k = block ? plan_block(h, s, C, &end) : plan_launch(h, s, C, &end);
+        const bool keep = block && s + k - 1 == C;
         tail = lbm_ctx::Tail();
         tail_flip = flips & 1;
         for (int p = 0; p < np && rc == LBM_OK; ++p) {
             hipStream_t st = p == 0 ? h->capture_stream : h->cap_part_stream;
             const lbm_ctx::Span& sp = multi ? h->part[p] : h->all;
-            rc = k >= 2 ? issue_fused(h, (int64_t)s, k, end, src, st, sp)
+            rc = k >= 2 ? (block ? issue_block(h, (int64_t)s, k, end, src, keep, st, sp)
+                                 : issue_fused(h, (int64_t)s, k, end, src, st, sp))
                         : issue_step(h, (int64_t)s, src, st, LBM_SCHED_BATCHED, sp);
         }
         if (k >= 2) {
             tail.k = k;
             tail.apply_shift = (h->K > 0 && (s - 1) % h->K == 0) ? 1 : 0;
             tail.checked = end == kEndCheck ? 1 : 0;
+            tail.kept = keep ? 1 : 0;
         }
         s += k;
         src = 1 - src;
@@ -1230,13 +1445,18 @@ static int step_loop(lbm_ctx* h, int64_t nsteps, bool multi) {
         // launch holds too few wavefronts to hide the marching latency
         // (Knudsen sweep: 4.0k MLUPS at five steps per launch, 17.1k single)
         int end = kEndPlain;
-        const int k = sched == LBM_SCHED_PER_INSTANCE ? 1 : plan_launch(h, m, h->steps + left, &end);
+        const bool block = h->block_on && sched != LBM_SCHED_PER_INSTANCE;
+        const int k = sched == LBM_SCHED_PER_INSTANCE ? 1
+                      : block ? plan_block(h, m, h->steps + left, &end) : plan_launch(h, m, h->steps + left, &end);
+        const bool keep = block && k == left;
         h->tail = lbm_ctx::Tail();
         if (k >= 2) {
             for (int p = 0; p < np; ++p) {
-                int rc = issue_fused(h, m, k, end, h->cur, stream_of(p), span_of_part(p));
+                int rc = block ? issue_block(h, m, k, end, h->cur, keep, stream_of(p), span_of_part(p))
+                               : issue_fused(h, m, k, end, h->cur, stream_of(p), span_of_part(p));
                 if (rc) return rc;
             }
+            h->tail.kept = keep ? 1 : 0;
             h->tail.k = k;
             h->tail.src = h->cur;
             h->tail.apply_shift = (h->K > 0 && (m - 1) % h->K == 0) ? 1 : 0;
@@ -1270,7 +1490,7 @@ int lbm_step(lbm_handle h, int64_t nsteps) {
         h->replayed = false;
         h->desc_saved = false;
     }
-    if (nsteps > 0 && !h->preloaded) {
+    if (nsteps > 0 && !h->preloaded && !h->block_on) {
         HIPCALL(h, preload_fused(h->storage, h->sr, h->layout == LBM_LAYOUT_CHUNKED, h->every_step, h->stream));
         h->preloaded = true;
     }
@@ -1343,11 +1563,11 @@ static int run_moments(lbm_ctx* h, int32_t k, int out_kind, void* T, void* qx, v
     // or (after a fused last launch) the readout buffer, replayed once
     int src = 1 - h->cur;
     if (h->steps > 0 && h->tail.k >= 2) {
-        if (!h->replayed) {
+        if (!h->replayed && !h->tail.kept) {
             int rc = replay_tail(h);
             if (rc) return rc;
         }
-        if (!h->every_step) {
+        if (!h->every_step && !h->tail.kept) {
             HIPCALL(h, launch_plane_moments(h->d_desc_last(), k, h->desc[k],
                                             reinterpret_cast<const double*>(h->buf(lbm_ctx::kReadout)), h->L.nodes,
                                             out_kind, T, qx, qy, in.t0, grad, partials, h->stream));
@@ -1514,6 +1734,7 @@ int lbm_set_step_fusion(lbm_handle h, int32_t steps) {
         return h->fail(LBM_EINVAL, "steps per launch must be 1 .. " + std::to_string(h->fuse_cap()) +
                                        " for this storage kind");
     h->fuse = steps;
+    h->block_on = false;
     h->drop_graphs();
     return LBM_OK;
 }
@@ -1563,6 +1784,7 @@ int lbm_set_launch_shape(lbm_handle h, const lbm_launch_shape* s) {
     h->shape.by = s->block_y;
     h->shape.xcd = s->xcd_remap ? 1 : 0;
     h->shape.nt = s->nontemporal ? 1 : 0;
+    h->block_on = false;
     build_tiles(h);
     h->drop_graphs();
     if (h->base) return upload_tables(h);
@@ -1607,7 +1829,7 @@ static std::string tune_key(lbm_ctx* h) {
     return b;
 }
 
-static bool cache_lookup(const char* path, const std::string& key, Shape* out, int* fuse) {
+static bool cache_lookup(const char* path, const std::string& key, Shape* out, int* fuse, bool* block) {
     FILE* fp = fopen(path, "r");
     if (!fp) return false;
     char line[512];
@@ -1622,6 +1844,9 @@ static bool cache_lookup(const char* path, const std::string& key, Shape* out, i
             *out = s;
             const char* f = strstr(line, "\"fuse\": ");
             *fuse = (f && f[8] >= '1' && f[8] <= '9') ? f[8] - '0' : 1;   // the digit after '"fuse": '
+            // lines written before there were block kernels: they replace single steps
+            const char* bl = strstr(line, "\"block\": ");
+            *block = bl ? bl[9] == '1' : *fuse == 1;
             found = true;   // the last matching line wins
         }
     }
@@ -1696,6 +1921,47 @@ static int time_fused(lbm_ctx* h, int k, int launches, hipEvent_t e0, hipEvent_t
     return LBM_OK;
 }
 
+// Average time per step of the block kernels' longest launches (of at most 32
+// steps for whole lattices).
+static int time_block(lbm_ctx* h, int steps, hipEvent_t e0, hipEvent_t e1, float* us) {
+    const int k = h->bplan.kind == kBlockWhole ? 32 : h->bplan.halo;
+    const int launches = (steps + k - 1) / k;
+    BlockArgs b;
+    StepArgs& a = b.s;
+    a.desc = h->d_desc();
+    a.tile_inst = h->d_btiles();
+    a.snap = nullptr;
+    a.partials = nullptr;
+    a.tile_base = 0;
+    a.ntiles = (int32_t)h->btile_inst.size();
+    a.seed = h->seed;
+    a.sr = h->sr;
+    a.ref = h->d_ref();
+    a.apply_shift = 0;
+    b.prev = nullptr;
+    b.steps = k;
+    b.halo = h->bplan.halo;
+    b.waves = h->bplan.waves;
+    b.win_x = h->bplan.win_x();
+    b.win_y = h->bplan.win_y();
+    int src = 0;
+    for (int w = 0; w < 2 + launches; ++w) {
+        if (w == 2) HIPCALL(h, hipEventRecord(e0, h->stream));
+        a.src = h->buf(src);
+        a.dst = h->buf(1 - src);
+        a.ctr_in = h->d_ctr() + src;
+        a.ctr_out = h->d_ctr() + (1 - src);
+        HIPCALL(h, launch_block(h->storage, h->bplan, h->shape, b, kEndPlain, h->stream));
+        src = 1 - src;
+    }
+    HIPCALL(h, hipEventRecord(e1, h->stream));
+    HIPCALL(h, hipEventSynchronize(e1));
+    float ms = 0.0f;
+    HIPCALL(h, hipEventElapsedTime(&ms, e0, e1));
+    *us = 1000.0f * ms / (k * launches);
+    return LBM_OK;
+}
+
 int lbm_autotune(lbm_handle h, int32_t steps, char* report, size_t report_len) {
     if (!valid(h)) return LBM_EINVAL;
     if (!h->base) return h->fail(LBM_ESTATE, "no device memory bound");
@@ -1706,11 +1972,15 @@ int lbm_autotune(lbm_handle h, int32_t steps, char* report, size_t report_len) {
     const char* path = getenv("LBM_AUTOTUNE_CACHE");
     Shape cached;
     int cached_fuse = 1;
-    if (path && *path && cache_lookup(path, key, &cached, &cached_fuse)) {
+    bool cached_block = false;
+    if (path && *path && cache_lookup(path, key, &cached, &cached_fuse, &cached_block)) {
         lbm_launch_shape ls = {cached.vec, cached.bx, cached.by, cached.xcd, cached.nt};
         if (report && report_len) snprintf(report, report_len, "{\"key\": \"%s\", \"cached\": true}", key.c_str());
         const int rc = lbm_set_launch_shape(h, &ls);
-        if (!rc) h->fuse = std::min(std::max(cached_fuse, 1), h->fuse_cap());
+        if (!rc) {
+            h->fuse = std::min(std::max(cached_fuse, 1), h->fuse_cap());
+            h->block_on = cached_block && h->bplan.kind != kBlockNone && (h->fuse == 1 || h->every_step);
+        }
         return rc;
     }
     // scratch contents: a fixed pattern of moderate finite values with
@@ -1789,10 +2059,16 @@ int lbm_autotune(lbm_handle h, int32_t steps, char* report, size_t report_len) {
             }
         }
     }
+    // the block kernels, which replace single steps (the same bits); for FP32
+    // storage and 16-bit storage rounding every step they replace fused
+    // launches too
+    float block_us = 1e30f;
+    if (!rc && h->bplan.kind != kBlockNone) rc = time_block(h, steps, e0, e1, &block_us);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    const int fuse = fused_us < best_us ? fused_k : 1;
+    const int fuse = fused_us < best_us && (!h->every_step || fused_us < block_us) ? fused_k : 1;
+    const bool block = fuse == 1 && block_us < best_us;
     // the planner's launch costs: the measured plain launches, the check
     // launches scaled from the built-in figures by the same ratio
     {
@@ -1810,21 +2086,28 @@ int lbm_autotune(lbm_handle h, int32_t steps, char* report, size_t report_len) {
              best.bx, best.by, best.xcd, best.nt, best_us, fused_us);
     rep += b;
     rep += "\"fused_timings_us\": [" + fused_rep + "], ";
-    snprintf(b, sizeof b, "\"steps_per_launch\": %d}", fuse);
+    if (h->bplan.kind != kBlockNone) {
+        snprintf(b, sizeof b, "\"block_us_per_step\": %.2f, ", block_us);
+        rep += b;
+    }
+    snprintf(b, sizeof b, "\"block_kernels\": %s, \"steps_per_launch\": %d}", block ? "true" : "false", fuse);
     rep += b;
     if (report && report_len) snprintf(report, report_len, "%s", rep.c_str());
     if (path && *path) {
         FILE* fp = fopen(path, "a");
         if (fp) {
             fprintf(fp, "{\"key\": \"%s\", \"vec\": %d, \"block_x\": %d, \"block_y\": %d, \"xcd\": %d, \"nt\": %d, "
-                        "\"us\": %.2f, \"fuse\": %d}\n",
-                    key.c_str(), best.vec, best.bx, best.by, best.xcd, best.nt, best_us, fuse);
+                        "\"us\": %.2f, \"fuse\": %d, \"block\": %d}\n",
+                    key.c_str(), best.vec, best.bx, best.by, best.xcd, best.nt, best_us, fuse, block ? 1 : 0);
             fclose(fp);
         }
     }
     lbm_launch_shape ls = {best.vec, best.bx, best.by, best.xcd, best.nt};
     rc = lbm_set_launch_shape(h, &ls);
-    if (!rc) h->fuse = fuse;
+    if (!rc) {
+        h->fuse = fuse;
+        h->block_on = block;
+    }
     return rc;
 }
 
