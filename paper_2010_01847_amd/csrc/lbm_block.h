@@ -154,7 +154,7 @@ __global__ __launch_bounds__(1024) void tile_kernel(BlockArgs b, int xcd, int no
                     apply_shift(g, rv);
                 }
                 const int y = gy[r];
-                if (xw || (d.bc_y != 0 && (y == 0 || y == ny - 1))) boundary(g, d, rv.wall_kd, gx, y);
+                if (xw || (d.bc_y != 0 && (y == 0 || y == ny - 1))) boundary<1>(g, d, rv.wall_kd, gx, y);
                 if constexpr (END == kEndCheck) {
                     if (s == K - 1) {
                         double E;
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(1024) void patch_kernel(BlockArgs b) {
         if (walled) {
 #pragma unroll
             for (int m = 0; m < M; ++m)
-                if (wall[m]) boundary(g[m], d, rv.wall_kd, x[m], y[m]);
+                if (wall[m]) boundary<1>(g[m], d, rv.wall_kd, x[m], y[m]);
         }
 #pragma unroll
         for (int m = 0; m < M; ++m) {

@@ -767,8 +767,7 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     if constexpr (END == kEndCheck) {
         // fixed-order wavefront sums; one record per tile (all 64 lanes are
         // active here: a wavefront leaves early only as a whole)
-#pragma unroll
-        for (int c = 0; c < kPartials; ++c) acc[c] = wave_sum(acc[c]);
+        wave_sums(acc);
         if (lane == 0) {
 #pragma unroll
             for (int c = 0; c < kPartials; ++c) a.partials[(int64_t)tg * kPartials + c] = acc[c];

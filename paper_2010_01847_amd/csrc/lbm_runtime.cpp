@@ -272,7 +272,7 @@ double block_cost(const std::vector<lbm_instance>& v, const BlockPlan& p, int st
     const double rounds = blocks / (cus * held);
     double step;
     if (p.kind == kBlockPatch) {
-        step = std::max(0.4, 0.125 * waves * held);
+        step = std::max(0.4, (held > 1.0 ? 0.13 : 0.11) * waves * held);
     } else {
         const double active = (double)(p.out_y() + p.halo - 1) / (p.waves * p.rows);   // rows still needed, mean
         step = 0.3 + 0.09 * waves * held * p.rows * active;
