@@ -73,7 +73,9 @@ typedef struct {
     int32_t nontemporal;    /* 1: streaming stores */
     int32_t tile_waves;     /* 1, 2, 4 or 8 wavefronts (64-node segments) along x */
     int32_t zchunk;         /* two steps per launch: planes each block marches through (>= 1;
-                               default 32) */
+                               32 in a new handle's shape, which then takes the range that
+                               fills its launches' last round of blocks until a shape is
+                               set) */
 } lbm3d_launch_shape;
 
 /* Message of the last failing call on this handle ("" if none); with NULL, the
@@ -155,7 +157,7 @@ int lbm3d_get_launch_shape(lbm3d_handle h, lbm3d_launch_shape* shape);
 /* Time every single-step tile shape (rows_per_tile x tile_waves) with and
  * without the XCD remap, then streaming stores on the fastest, then two steps
  * per launch over z ranges of 16, 32 and 64 planes, each with and without
- * streaming stores, for `steps` steps each (0 selects 20) on buffers filled
+ * streaming stores (and a new handle's own z range), for `steps` steps each (0 selects 20) on buffers filled
  * with a fixed pattern of moderate finite values; keep the fastest shape, z
  * range, store kind and steps per launch.  Must run before lbm3d_init (it
  * overwrites the buffers).  report, if not NULL, receives a JSON summary

@@ -74,6 +74,8 @@ constexpr int kPairNW = PLBM3_PAIR_WAVES;
 // Fewest two-step tiles (blocks) for which two steps per launch are the
 // default: one per CU.
 constexpr int64_t kPairMinTiles = 256;
+// Two-step blocks that run at once: one per CU.
+constexpr int64_t kZBlocks = 256;
 struct PairArgs {
     Geometry g;
     Coeffs c;

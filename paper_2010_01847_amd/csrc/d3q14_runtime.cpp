@@ -125,6 +125,33 @@ struct lbm3d_ctx {
                               ((cfg.nz + shape.zchunk - 1) / shape.zchunk);
         fuse = tiles >= kPairMinTiles ? 2 : 1;
     }
+    bool zauto = true;           // z ranges by z_range() (no launch shape was set)
+    // Planes per block of the two-step kernel.  A block marches through its z
+    // range and two halo planes at each end, one block per CU, so a launch
+    // takes about (rounds of kZBlocks blocks) x (range + 4) plane times; the
+    // range that makes that least fills the last round.  Measured (us per
+    // step, range 32 / this one): 301 x 211 x 163 BF16 152 / 125 (24 planes),
+    // FP32 211 / 186; 192^3 99.8 / 77.2 (48) and 125 / 99.6; 130 x 500 x 300
+    // 273 / 233 (150) and 389 / 353; 512^3 BF16 1309 / 1251 (57).  FP32 keeps
+    // 32 planes unless the count falls by 6%: 512^3 runs 1879 us per step at
+    // 32 and 1938 at 57 (5% fewer plane times, but the halo planes of blocks
+    // further apart in z miss the caches).
+    static int z_range(int nx, int ny, int nz, int storage) {
+        const int64_t cols = (int64_t)((nx + kPairW3 - 1) / kPairW3) * ((ny + kPairYO - 1) / kPairYO);
+        auto planes = [&](int zc) { return (cols * ((nz + zc - 1) / zc) + kZBlocks - 1) / kZBlocks * (zc + 4); };
+        const int dflt = std::min(32, nz);
+        int best = dflt;
+        int64_t least = planes(dflt) * (storage == LBM_F32 ? 94 : 100) / 100;
+        for (int k = 1; k <= (nz + 7) / 8; ++k) {
+            const int zc = (nz + k - 1) / k;
+            if (planes(zc) < least) {
+                least = planes(zc);
+                best = zc;
+            }
+        }
+        return best;
+    }
+    int zrange() const { return zauto ? z_range(cfg.nx, cfg.ny, cfg.nz, cfg.storage) : shape.zchunk; }
     double tau = 0, beta = 1, s = 1, cv = 1;
     Coeffs co{};
     char* base = nullptr;
@@ -325,7 +352,7 @@ int lbm3d_step(lbm3d_handle h, int64_t nsteps) {
     // measured 71.1 vs 56.9 GLUPS without (512^3 FP32, 32-plane ranges)
     p.xcd_remap = 1;
     p.nontemporal = a.nontemporal;
-    p.zchunk = h->shape.zchunk;
+    p.zchunk = h->zrange();
     p.ptx = (uint32_t)((h->cfg.nx + kPairW3 - 1) / kPairW3);
     p.pty = (uint32_t)((h->cfg.ny + kPairYO - 1) / kPairYO);
     p.ptz = (uint32_t)((h->cfg.nz + p.zchunk - 1) / p.zchunk);
@@ -438,6 +465,7 @@ int lbm3d_set_launch_shape(lbm3d_handle h, const lbm3d_launch_shape* shape) {
         return h->fail(LBM_EINVAL, "xcd_remap and nontemporal must be 0 or 1");
     if (shape->zchunk < 1) return h->fail(LBM_EINVAL, "zchunk must be >= 1");
     h->shape = *shape;
+    h->zauto = false;
     // the tiling changes, the buffers (which do not depend on it) stay
     const Layout3 L = layout_of(h->cfg, r, tw);
     h->L.g = L.g;
@@ -516,16 +544,19 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
         sh.nontemporal = 1;
         try_shape(sh);
     }
-    // two steps per launch over z ranges of 16, 32 and 64 planes, with and
-    // without streaming stores (per-step time over the same number of steps,
-    // rounded up to pairs); the two-step kernel's tile is fixed, so the
-    // single-step kernel's best store kind need not be its best
+    // two steps per launch over z ranges of 16, 32 and 64 planes (reported) and
+    // the one a new handle takes, with and without streaming stores (per-step
+    // time over the same number of steps, rounded up to pairs); the two-step
+    // kernel's tile is fixed, so the single-step kernel's best store kind need
+    // not be its best
     const float single_us = best_us;
     float pair_us = 1e30f;
     int best_z = best.zchunk, best_nt = best.nontemporal;
     std::string prep;
     steps += steps & 1;
-    for (int zc : {16, 32, 64}) {
+    const int zdef = lbm3d_ctx::z_range(h->cfg.nx, h->cfg.ny, h->cfg.nz, h->cfg.storage);
+    for (int cand = 0; cand < 4; ++cand) {
+        const int zc = cand < 3 ? 16 << cand : zdef;
         for (int nt = 0; nt < 2; ++nt) {
             if (rc) break;
             lbm3d_launch_shape sh = best;
@@ -545,7 +576,7 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
             const float us = 1e3f * ms / (float)steps;
             char b[64];
             snprintf(b, sizeof b, "%s[%d, %d, %.2f]", prep.empty() ? "" : ", ", zc, nt, us);
-            prep += b;
+            if (cand < 3) prep += b;
             if (us < pair_us) {
                 pair_us = us;
                 best_z = zc;
