@@ -563,17 +563,28 @@ hipError_t launch_plane_moments(const InstDesc* d_desc, int inst, const InstDesc
 // CH: chunked layout, whose direction runs are kChunkPlane elements apart, so
 // that the eight loads or stores of a row share one address and differ by
 // immediate offsets.
+// The first kDelayLevels levels keep their c_y = +1 movers (two rows of three
+// values) in LDS, 1.5 KB per level and wavefront, the others in registers.  The
+// kernel is bound by VALU issue, which more wavefronts per SIMD fill better:
+// 90-96 VGPRs instead of 114-128 allow five instead of four, whose LDS (120 KB
+// of a CU's 160) four levels leave room for.  Reading a level back at the
+// neighbouring lanes' addresses also saves its two diagonal DPP pulls and six
+// moves.  Measured (8192^2, us per step, all in registers / this): FP16-SR
+// 159.5 / 145.6, FP16 154.6 / 139.6, BF16-SR 163 / 156, F16_SPLIT 167 / 153,
+// BF16_SPLIT 168 / 154, FP32 179.4 / 177.2 (bound by its HBM traffic there;
+// 3000 x 2500: 27.3 / 23.9).  At four wavefronts per SIMD the LDS form is 2%
+// slower than registers; five levels leave LDS for four (FP16-SR 164); all
+// five delayed movers of three levels 145.7, of two 163 (105 VGPRs).
+constexpr int kDelayLevels = 4;
 // Waves per SIMD the register allocation must leave room for (1: no
-// constraint).  The plain seven-step FP32 launch would take 130 VGPRs, three
-// waves per SIMD; held to 128 (four waves, two registers spilled) it runs
-// 1,230 instead of 1,383 us per launch on 8192^2.
-template <class S, int K, int END>
+// constraint).
+template <int END>
 struct MarchWaves {
-    static constexpr int value = (sizeof(S) == 4 && K == 7 && END == kEndPlain) ? 4 : 1;
+    static constexpr int value = END == kEndPlain ? 5 : 1;
 };
 
 template <class S, int SR, int SPLIT, int K, int KMAX, int END, int CH, int RM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MarchWaves<S, K, END>::value)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MarchWaves<END>::value)))
 void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     static_assert(K >= 2 && K <= KMAX, "stages per launch");
     static_assert(RM == kRoundEvery || sizeof(S) == 2, "FP32 storage rounds every step");
@@ -633,6 +644,18 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
 
     // per level l (0: loaded rows, l: results of stage l), the c_y = 0 movers of
     // the previous row and the c_y = +1 movers of the two previous rows
+    // (levels below DL keep the c_y = +1 movers in LDS, in the slots of the
+    // last two rows; `par`: the slot this iteration reads and refills.  A
+    // wavefront touches its own part only, in program order: no barrier.)
+    constexpr int DL = K < kDelayLevels ? K : kDelayLevels;
+    __shared__ float delay[4][DL][2][3][64];
+    const uint32_t mine = (threadIdx.x >> 6) * (uint32_t)sizeof(delay[0]);
+    const uint32_t at_c = mine + (uint32_t)lane * 4u, at_l = mine + (uint32_t)((lane - 1) & 63) * 4u,
+                   at_r = mine + (uint32_t)((lane + 1) & 63) * 4u;
+    uint32_t par = 0u;
+    auto delayed = [&](uint32_t at) -> float& {
+        return *reinterpret_cast<float*>(reinterpret_cast<char*>(&delay[0][0][0][0][0]) + at);
+    };
     float mid[K][2], up1[K][3], up2[K][3];
 #pragma unroll
     for (int l = 0; l < K; ++l) {
@@ -671,7 +694,13 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
             float out[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
             if (!WARM || it >= 2 * s) {
                 float g[8];
-                march_gather(cur, mid[s - 1], up2[s - 1], g);
+                if (s - 1 < DL) {
+                    const uint32_t o = (uint32_t)((s - 1) * sizeof(delay[0][0])) + par;
+                    float up[3] = {delayed(at_c + o), delayed(at_l + o + 256), delayed(at_r + o + 512)};
+                    march_gather<1>(cur, mid[s - 1], up, g);
+                } else {
+                    march_gather<0>(cur, mid[s - 1], up2[s - 1], g);
+                }
                 if (s < K) {
                     const int gy = wrapm(yi - s, ny, kMarchRows + 2 * K + PF);
                     if (s == 1 && a.apply_shift) {
@@ -742,10 +771,16 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
                 }
             }
             // level s - 1 moves one row on (its values are valid whenever a later stage reads them)
+            if (s - 1 < DL) {
+                const uint32_t o = (uint32_t)((s - 1) * sizeof(delay[0][0])) + par;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                up2[s - 1][k] = up1[s - 1][k];
-                up1[s - 1][k] = cur[yup(k)];
+                for (int k = 0; k < 3; ++k) delayed(at_c + o + 256 * k) = cur[yup(k)];
+            } else {
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    up2[s - 1][k] = up1[s - 1][k];
+                    up1[s - 1][k] = cur[yup(k)];
+                }
             }
 #pragma unroll
             for (int k = 0; k < 2; ++k) mid[s - 1][k] = cur[ymid(k)];
@@ -761,8 +796,8 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     };
     // iters >= 2 K + 1: the warm-up always completes
     int it = 0;
-    for (; it < 2 * K; ++it) iteration(it, std::true_type{});
-    for (; it < iters; ++it) iteration(it, std::false_type{});
+    for (; it < 2 * K; ++it, par ^= (uint32_t)sizeof(delay[0][0][0])) iteration(it, std::true_type{});
+    for (; it < iters; ++it, par ^= (uint32_t)sizeof(delay[0][0][0])) iteration(it, std::false_type{});
     if (t == 0 && lane == 0) a.ctr_out[0] = step + (uint32_t)K;
     if constexpr (END == kEndCheck) {
         // fixed-order wavefront sums; one record per tile (all 64 lanes are

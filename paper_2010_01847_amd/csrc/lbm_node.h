@@ -527,14 +527,16 @@ __device__ __forceinline__ float xpull(float v) {
 }
 
 // Pulled populations of one stage: direction i from the row at y - c_iy
-// (dn: the newest row, mid: one row back, up: two rows back), shifted by c_ix.
+// (dn: the newest row, mid: one row back, up: two rows back), shifted by c_ix
+// (UP_SHIFTED: up is given shifted).
+template <int UP_SHIFTED = 0>
 __device__ __forceinline__ void march_gather(const float dn_row[8], const float mid[2], const float up[3], float g[8]) {
     g[0] = xpull<0>(mid[0]);
     g[2] = xpull<2>(mid[1]);
-    g[1] = xpull<1>(up[0]);
-    g[4] = xpull<4>(up[1]);
-    g[5] = xpull<5>(up[2]);
-    g[3] = xpull<3>(dn_row[3]);
+    g[1] = up[0];
+    g[4] = UP_SHIFTED ? up[1] : xpull<4>(up[1]);
+    g[5] = UP_SHIFTED ? up[2] : xpull<5>(up[2]);
+    g[3] = dn_row[3];
     g[6] = xpull<6>(dn_row[6]);
     g[7] = xpull<7>(dn_row[7]);
 }
