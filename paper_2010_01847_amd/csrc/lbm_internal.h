@@ -187,6 +187,10 @@ struct StepArgs {
     uint32_t* ctr_out;          // written with ctr_in + steps by the launch's first tile
     uint32_t seed;              // stream of the stochastic-rounding bits
     int32_t sr;                 // 1: round stores stochastically (nodes per lane must be 1)
+    // kEndMoments: the moments of instance out_inst also go to the caller's
+    // FP64 arrays (ny nx each; null: not wanted)
+    int32_t out_inst = -1;
+    double* out[3] = {nullptr, nullptr, nullptr};
 };
 
 // How the block kernels (lbm_block.h) hold a handle's lattices on the chip:

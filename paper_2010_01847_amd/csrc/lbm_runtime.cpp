@@ -1566,9 +1566,14 @@ int lbm_step(lbm_handle h, int64_t nsteps) {
 // whole launch is replayed instead, ending with kEndMoments: the FP64 moments
 // of its step-n nodes go to the readout buffer (as planes laid out like the
 // snapshot), from the same registers the launch itself relaxed.
-static int replay_tail(lbm_ctx* h) {
+// That launch also writes the moments of instance k to the arrays of `out`.
+static int replay_tail(lbm_ctx* h, int32_t k = -1, double* const* out = nullptr) {
     const lbm_ctx::Tail& t = h->tail;
     StepArgs a;
+    if (out) {
+        a.out_inst = k;
+        for (int c = 0; c < 3; ++c) a.out[c] = out[c];
+    }
     a.desc = h->d_desc_last();
     a.src = h->buf(t.src);
     a.dst = h->buf(lbm_ctx::kReadout);
@@ -1603,6 +1608,7 @@ static int replay_tail(lbm_ctx* h) {
 }
 
 static int run_moments(lbm_ctx* h, int32_t k, int out_kind, void* T, void* qx, void* qy, DD* partials) {
+    double* const out[3] = {static_cast<double*>(T), static_cast<double*>(qx), static_cast<double*>(qy)};
     const lbm_instance& in = h->inst[k];
     const double grad = in.bc_x == LBM_BC_GRADIENT ? in.grad_x : 0.0;
     // after a check step the reference has moved and its shift is still pending
@@ -1612,8 +1618,11 @@ static int run_moments(lbm_ctx* h, int32_t k, int out_kind, void* T, void* qx, v
     int src = 1 - h->cur;
     if (h->steps > 0 && h->tail.k >= 2) {
         if (!h->replayed && !h->tail.kept) {
-            int rc = replay_tail(h);
-            if (rc) return rc;
+            // a 16-bit replay forms the moments themselves: FP64 arrays are
+            // written by it, without a pass over the readout buffer
+            const bool direct = !h->every_step && out_kind == 1 && !partials;
+            int rc = replay_tail(h, k, direct ? out : nullptr);
+            if (rc || direct) return rc;
         }
         if (!h->every_step && !h->tail.kept) {
             HIPCALL(h, launch_plane_moments(h->d_desc_last(), k, h->desc[k],
