@@ -142,7 +142,10 @@ int lbm3d_totals(lbm3d_handle h, double out[4]);
  * either way; 16-bit storage otherwise rounds one state per launch, so its
  * results depend on the steps per launch (see LBM_FLAG_ROUND_EVERY_STEP).
  * Default: 2 when the box holds at least 256 such blocks (60 x 12 nodes of 32
- * planes each: one per CU), else 1.  Errors: EINVAL (steps not 1 or 2). */
+ * planes each: one per CU), else 1.  A new FP32 handle whose default is 2
+ * takes three steps per launch where that is the faster (same results; it
+ * still reports 2) until the steps per launch or a launch shape are set.
+ * Errors: EINVAL (steps not 1 or 2). */
 int lbm3d_set_step_fusion(lbm3d_handle h, int32_t steps);
 
 /* The current time steps per launch (1 or 2); -1 for an invalid handle. */
@@ -157,7 +160,7 @@ int lbm3d_get_launch_shape(lbm3d_handle h, lbm3d_launch_shape* shape);
 /* Time every single-step tile shape (rows_per_tile x tile_waves) with and
  * without the XCD remap, then streaming stores on the fastest, then two steps
  * per launch over z ranges of 16, 32 and 64 planes, each with and without
- * streaming stores (and a new handle's own z range), for `steps` steps each (0 selects 20) on buffers filled
+ * streaming stores (and a new handle's own z range and steps per launch), for `steps` steps each (0 selects 20) on buffers filled
  * with a fixed pattern of moderate finite values; keep the fastest shape, z
  * range, store kind and steps per launch.  Must run before lbm3d_init (it
  * overwrites the buffers).  report, if not NULL, receives a JSON summary

@@ -526,6 +526,8 @@ hipError_t launch_pair(int storage, int sr, int every_step, const PairArgs& a, h
     return hipGetLastError();
 }
 
+#include "d3q14_triple.h"
+
 // Instantiate kernel K<S, L> for the storage and layout of a call.
 #define PLBM3_DISPATCH(storage, layout, CALL)                         \
     switch ((storage) * 2 + ((layout) ? 1 : 0)) {                     \

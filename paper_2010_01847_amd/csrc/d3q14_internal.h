@@ -93,6 +93,16 @@ struct PairArgs {
 // type as well (the same bits as two single steps); FP32 always does.
 hipError_t launch_pair(int storage, int sr, int every_step, const PairArgs& a, hipStream_t st);
 
+// Three steps per launch, FP32 (d3q14_triple.h): blocks of kDeepWaves
+// wavefronts own kDeepXO x kDeepYO output nodes of each plane of a z range.
+constexpr int kDeepSteps = 3, kDeepRows = 2, kDeepWaves = 12;
+constexpr int kDeepXO = 64 - 2 * kDeepSteps, kDeepYO = kDeepRows * kDeepWaves - 2 * kDeepSteps;
+// Lane offsets within a row are 32-bit byte offsets.
+inline bool deep_fits(const Geometry& g) {
+    return (int64_t)(g.layout ? g.nseg * (kQ * kTileX) : g.pitch) * 4 <= INT32_MAX;
+}
+hipError_t launch_triple(int sr, const PairArgs& a, hipStream_t st);
+
 // Fill `bytes` (a multiple of 4) with the timing scratch pattern of the
 // device file (moderate finite values in every storage type, changing bits).
 hipError_t launch_fill(void* buf, size_t bytes, uint32_t seed, hipStream_t st);

@@ -113,7 +113,7 @@ struct lbm3d_ctx {
     hipStream_t stream = nullptr;
     Layout3 L{};
     lbm3d_launch_shape shape{4, 1, 0, 1, 32};
-    int fuse = 1;                // time steps per launch (1, or 2 with the z-marching kernel)
+    int fuse = 1;                // time steps per launch (1, or 2 with the z-marching kernel; see deep())
     // two steps per launch when the z-marching tiles fill the chip (one block
     // per CU): a launch takes about one tile's marching time, so small boxes
     // run single steps (measured FP32 us per step, single / two: 64^3 5.3 /
@@ -136,22 +136,49 @@ struct lbm3d_ctx {
     // 32 planes unless the count falls by 6%: 512^3 runs 1879 us per step at
     // 32 and 1938 at 57 (5% fewer plane times, but the halo planes of blocks
     // further apart in z miss the caches).
-    static int z_range(int nx, int ny, int nz, int storage) {
-        const int64_t cols = (int64_t)((nx + kPairW3 - 1) / kPairW3) * ((ny + kPairYO - 1) / kPairYO);
-        auto planes = [&](int zc) { return (cols * ((nz + zc - 1) / zc) + kZBlocks - 1) / kZBlocks * (zc + 4); };
-        const int dflt = std::min(32, nz);
-        int best = dflt;
-        int64_t least = planes(dflt) * (storage == LBM_F32 ? 94 : 100) / 100;
-        for (int k = 1; k <= (nz + 7) / 8; ++k) {
-            const int zc = (nz + k - 1) / k;
-            if (planes(zc) < least) {
-                least = planes(zc);
-                best = zc;
+    struct Range {
+        int planes;              // per block
+        int64_t rounds, cost;    // rounds of kZBlocks blocks; plane times
+    };
+    // Columns of xo x yo nodes, `halo` extra planes per range, and the percentage
+    // of the cost at 32 planes that a range has to stay below to replace it.
+    static Range z_range(const lbm3d_config& c, int xo, int yo, int halo, int percent) {
+        const int64_t cols = (int64_t)((c.nx + xo - 1) / xo) * ((c.ny + yo - 1) / yo);
+        auto at = [&](int zc) {
+            const int64_t r = (cols * ((c.nz + zc - 1) / zc) + kZBlocks - 1) / kZBlocks;
+            return Range{zc, r, r * (zc + halo)};
+        };
+        Range best = at(std::min(32, (int)c.nz));
+        int64_t least = best.cost * percent / 100;
+        for (int k = 1; k <= (c.nz + 7) / 8; ++k) {
+            const Range r = at((c.nz + k - 1) / k);
+            if (r.cost < least) {
+                least = r.cost;
+                best = r;
             }
         }
         return best;
     }
-    int zrange() const { return zauto ? z_range(cfg.nx, cfg.ny, cfg.nz, cfg.storage) : shape.zchunk; }
+    Range pair_range() const { return z_range(cfg, kPairW3, kPairYO, 4, cfg.storage == LBM_F32 ? 94 : 100); }
+    Range deep_range() const { return z_range(cfg, kDeepXO, kDeepYO, 2 * kDeepSteps, 97); }
+    int zrange() const { return zauto ? pair_range().planes : shape.zchunk; }
+    bool fauto = true;           // steps per launch chosen here (no explicit setting)
+    // Three steps per launch (FP32 only; the same bits) instead of two, where
+    // neither the launch shape nor the steps per launch were set.  A plane
+    // costs a block of three steps 2.5 .. 2.8 us per step and one of two 1.8 ..
+    // 2.3, so it pays where its ranges need clearly fewer plane times, and
+    // unless one round of blocks holds the whole box (two steps then often run
+    // faster, with less than the full traffic).  Measured (us per step, two /
+    // three; ratio of plane times): 512^3 1745 / 1622 (0.72), 301 x 211 x 163
+    // 187 / 157 (0.71), 607 x 241 x 629 1412 / 1177 (0.69), 428 x 201 x 121 163
+    // / 159 (0.71), and on the other side 160 x 402 x 492 405 / 425 (0.74); in
+    // one round 256^3 240 / 253, 191 x 179 x 282 142 / 146, 192^3 103 / 119.
+    bool deep_pays() const {
+        if (cfg.storage != LBM_F32 || !deep_fits(L.g)) return false;
+        const Range p = pair_range();
+        return p.rounds >= 2 && deep_range().cost * 100 < p.cost * 73;
+    }
+    bool deep() const { return fuse == 2 && fauto && zauto && deep_pays(); }
     double tau = 0, beta = 1, s = 1, cv = 1;
     Coeffs co{};
     char* base = nullptr;
@@ -344,7 +371,7 @@ int lbm3d_step(lbm3d_handle h, int64_t nsteps) {
     a.xcd_remap = h->shape.xcd_remap;
     a.nontemporal = h->shape.nontemporal;
     const int sr = (h->cfg.flags & LBM_FLAG_STOCHASTIC_ROUNDING) ? 1 : 0;
-    PairArgs p;
+    PairArgs p, t;
     p.g = a.g;
     p.c = a.c;
     p.seed = a.seed;
@@ -357,7 +384,25 @@ int lbm3d_step(lbm3d_handle h, int64_t nsteps) {
     p.pty = (uint32_t)((h->cfg.ny + kPairYO - 1) / kPairYO);
     p.ptz = (uint32_t)((h->cfg.nz + p.zchunk - 1) / p.zchunk);
     p.ntiles = p.ptx * p.pty * p.ptz;
+    t = p;
+    const bool deep = h->deep();
+    t.zchunk = h->deep_range().planes;
+    t.ptx = (uint32_t)((h->cfg.nx + kDeepXO - 1) / kDeepXO);
+    t.pty = (uint32_t)((h->cfg.ny + kDeepYO - 1) / kDeepYO);
+    t.ptz = (uint32_t)((h->cfg.nz + t.zchunk - 1) / t.zchunk);
+    t.ntiles = t.ptx * t.pty * t.ptz;
     for (int64_t k = 0; k < nsteps;) {
+        const int64_t left = nsteps - k;
+        if (deep && left >= kDeepSteps && left != 4) {   // four: two launches of two
+            t.src = h->buf(h->cur);
+            t.dst = h->buf(1 - h->cur);
+            t.step = (uint32_t)h->steps;
+            HIPCALL3(h, launch_triple(sr, t, h->stream));
+            h->cur = 1 - h->cur;
+            h->steps += kDeepSteps;
+            k += kDeepSteps;
+            continue;
+        }
         if (h->fuse == 2 && nsteps - k >= 2) {
             p.src = h->buf(h->cur);
             p.dst = h->buf(1 - h->cur);
@@ -476,6 +521,7 @@ int lbm3d_set_step_fusion(lbm3d_handle h, int32_t steps) {
     if (!valid3(h)) return LBM_EINVAL;
     if (steps != 1 && steps != 2) return h->fail(LBM_EINVAL, "steps per launch must be 1 or 2");
     h->fuse = steps;
+    h->fauto = false;
     return LBM_OK;
 }
 
@@ -545,18 +591,23 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
         try_shape(sh);
     }
     // two steps per launch over z ranges of 16, 32 and 64 planes (reported) and
-    // the one a new handle takes, with and without streaming stores (per-step
-    // time over the same number of steps, rounded up to pairs); the two-step
-    // kernel's tile is fixed, so the single-step kernel's best store kind need
-    // not be its best
+    // the one a new handle takes, and three where a new handle takes them, with
+    // and without streaming stores (per-step time over the same number of
+    // steps, rounded up to whole launches); these kernels' tiles are fixed, so
+    // the single-step kernel's best store kind need not be theirs
     const float single_us = best_us;
     float pair_us = 1e30f;
     int best_z = best.zchunk, best_nt = best.nontemporal;
     std::string prep;
     steps += steps & 1;
-    const int zdef = lbm3d_ctx::z_range(h->cfg.nx, h->cfg.ny, h->cfg.nz, h->cfg.storage);
-    for (int cand = 0; cand < 4; ++cand) {
+    bool best_deep = false;
+    const int zdef = h->pair_range().planes;
+    for (int cand = 0; cand < 5; ++cand) {
         const int zc = cand < 3 ? 16 << cand : zdef;
+        if (cand == 4) {
+            if (!h->deep_pays()) break;
+            steps = (steps + 5) / 6 * 6;
+        }
         for (int nt = 0; nt < 2; ++nt) {
             if (rc) break;
             lbm3d_launch_shape sh = best;
@@ -564,7 +615,8 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
             sh.nontemporal = nt;
             rc = lbm3d_set_launch_shape(h, &sh);
             h->fuse = 2;
-            if (!rc) rc = lbm3d_step(h, 2);
+            if (cand == 4) h->zauto = h->fauto = true;
+            if (!rc) rc = lbm3d_step(h, 6);
             if (!rc && (e = hipEventRecord(e0, h->stream)) != hipSuccess) rc = h->hip_fail(e, "hipEventRecord");
             if (!rc) rc = lbm3d_step(h, steps);
             if (!rc && (e = hipEventRecord(e1, h->stream)) != hipSuccess) rc = h->hip_fail(e, "hipEventRecord");
@@ -581,6 +633,7 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
                 pair_us = us;
                 best_z = zc;
                 best_nt = nt;
+                best_deep = cand == 4;
             }
         }
     }
@@ -598,6 +651,7 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
     }
     rc = lbm3d_set_launch_shape(h, &best);
     if (rc) return rc;
+    if (h->fuse == 2 && best_deep) h->zauto = h->fauto = true;
     char b[128];
     snprintf(b, sizeof b, "], \"best\": [%d, %d, %d, %d, %.2f], \"pair_us_per_step\": [", best.rows_per_tile,
              best.xcd_remap, best.nontemporal, best.tile_waves, single_us);
