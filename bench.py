@@ -74,8 +74,10 @@ BYTES_PER_NODE_3D = {"f32": 112, "f16": 56, "bf16": 56}
 BOUND = {"f32": 1e-5, "f16": 5e-3, "bf16": 5e-3, "f16_split": 5e-3, "bf16_split": 5e-3}
 _CSRC = os.path.join(ROOT, "paper_2010_01847_amd", "csrc")
 # the device code and the headers that fix its tiles, descriptors and rounding
-KERNEL_SOURCES = [os.path.join(_CSRC, f) for f in ("lbm_device.hip", "lbm_internal.h", "lbm_numeric.h")]
-KERNEL_SOURCES_3D = [os.path.join(_CSRC, f) for f in ("d3q14_device.hip", "d3q14_internal.h", "lbm_numeric.h")]
+KERNEL_SOURCES = [os.path.join(_CSRC, f) for f in ("lbm_device.hip", "lbm_internal.h", "lbm_node.h",
+                                                     "lbm_numeric.h")]
+KERNEL_SOURCES_3D = [os.path.join(_CSRC, f) for f in ("d3q14_device.hip", "d3q14_internal.h", "d3q14_triple.h",
+                                                        "lbm_numeric.h")]
 PROFILES = os.path.join(ROOT, "profiles")
 
 
@@ -394,8 +396,8 @@ def _run_d3q14(args, torch, W, n_sample=4096):
     """D3Q14 thermal-wave box: periodic n^3 (n = 512 by default), T0 = 1 plus
     16 seeded Fourier modes (wave numbers up to 8 per axis, total amplitude
     1e-3), tau_N = 0.6, tau_R = 5, no initial flux; chunked layout, launch
-    shape and steps per launch (one, or two with the z-marching kernel) chosen
-    by the library's autotuner.  The per-launch time is the HIP-event time
+    shape and steps per launch (one, or two or three with the z-marching
+    kernels) chosen by the library's autotuner.  The per-launch time is the HIP-event time
     over the timed steps (consecutive launches on one stream) divided by the
     number of launches.  Each row's fields at n_sample seeded nodes after the
     timed steps."""
@@ -414,7 +416,7 @@ def _run_d3q14(args, torch, W, n_sample=4096):
         box = Box(case.nx, case.ny, case.nz, case.tau_n, case.tau_r, storage=st, scale=scale,
                   stochastic=rnd == "stochastic", seed=1847)
         if args.d3q14_shape == "auto":
-            fuse = box.autotune(10)["steps_per_launch"]
+            fuse = box.autotune(10)["launch_steps"]
         else:
             vals = [int(v) for v in args.d3q14_shape.split(",")]
             box.set_launch_shape(*vals[:5])
@@ -432,7 +434,7 @@ def _run_d3q14(args, torch, W, n_sample=4096):
         box.close()
         torch.cuda.empty_cache()
         # algorithmic bytes per launch: 14 reads + 14 writes per update, times
-        # the updates one launch performs (fuse = 2 for the z-marching kernel)
+        # the updates one launch performs (fuse = 2 or 3 for the z-marching kernels)
         gbs = BYTES_PER_NODE_3D[st] * nodes / (ms / 1e3) / 1e9
         out["rows"].append({"storage": st, "rounding": rnd, "mlups": round(nodes / (ms / 1e3) / 1e6, 1),
                             "ms_per_step": round(ms, 4), "steps_per_launch": fuse,
@@ -442,10 +444,9 @@ def _run_d3q14(args, torch, W, n_sample=4096):
     f32 = [r for r in out["rows"] if r["storage"] == "f32"]
     if f32:
         r = f32[0]
-        two = r["steps_per_launch"] == 2
+        kind = {1: "", 2: "_pair", 3: "_triple"}[r["steps_per_launch"]]
         traffic = _traffic_from(os.path.join(
-            PROFILES, f"stream_collide_d3q14_f32{'_pair' if two else ''}_thermal_waves_{case.nx}.md"),
-            KERNEL_SOURCES_3D)
+            PROFILES, f"stream_collide_d3q14_f32{kind}_thermal_waves_{case.nx}.md"), KERNEL_SOURCES_3D)
         # compulsory bytes of one launch: the state read once and written once;
         # achieved from the counters' bytes while the profile is current
         compulsory = BYTES_PER_NODE_3D["f32"] * nodes
@@ -458,8 +459,10 @@ def _run_d3q14(args, torch, W, n_sample=4096):
                            "traffic": traffic,
                            "achieved_bytes": "measured (rocprofv3 counters)" if traffic is not None else
                                              "compulsory (profile stale)",
-                           "kernel": ("d3q14 pair_kernel (two steps per launch, z-marching)" if two
-                                      else "d3q14 step_kernel"),
+                           "kernel": {1: "d3q14 step_kernel",
+                                      2: "d3q14 pair_kernel (two steps per launch, z-marching)",
+                                      3: "d3q14 triple_kernel (three steps per launch, z-marching)"}[
+                                          r["steps_per_launch"]],
                            "steps_per_launch": r["steps_per_launch"], "kernel_us": r["launch_us"],
                            "bytes_per_launch": moved,
                            "compulsory": {"bytes_per_launch": compulsory, "gbs": round(compulsory / t / 1e9, 1),

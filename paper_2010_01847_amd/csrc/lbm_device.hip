@@ -526,7 +526,7 @@ hipError_t launch_plane_moments(const InstDesc* d_desc, int inst, const InstDesc
 //
 // Temporal blocking without LDS or barriers: K time steps per pass over HBM.
 // A wavefront owns a 64-column window (W = 64 - 2 KMAX output columns and a
-// KMAX-node halo on each side, periodic images) of a chunk of kMarchRows
+// KMAX-node halo on each side, periodic images) of a chunk of march_rows
 // output rows and marches along y.  Iteration `it` loads input row
 // yi = y0 - K + it and runs K stages: stage s advances row yi - s from the
 // rows of level s - 1 (level 0: loaded, level s: advanced s steps), on lanes
@@ -617,10 +617,10 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     const int local = tg - d.p_tile_begin;
     const int ty = local / d.p_tiles_x;
     const int tx = local - ty * d.p_tiles_x;
-    const int x0 = tx * W, y0 = ty * kMarchRows;
+    const int x0 = tx * W, y0 = ty * a.march_rows;
     const int nx = d.nx, ny = d.ny;
     const int gx = wrapm(x0 - KMAX + lane, nx, 64);
-    const int iters = min(kMarchRows, ny - y0) + 2 * K;
+    const int iters = min(a.march_rows, ny - y0) + 2 * K;
     const uint32_t step = a.ctr_in[0];
     const S* __restrict__ src = reinterpret_cast<const S*>(a.src) + d.off;
     S* __restrict__ dst = reinterpret_cast<S*>(a.dst) + d.off;
@@ -635,7 +635,7 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     // raw loads of input row yi (converted only where the row is used, so
     // the loads stay in flight across the iterations in between)
     auto fetch_row = [&](int yi, S v[8], float& E) {
-        const int gy = wrapm(yi, ny, kMarchRows + 2 * K + PF);
+        const int gy = wrapm(yi, ny, a.march_rows + 2 * K + PF);
         const S* row = src + (int64_t)gy * d.row;
 #pragma unroll
         for (int i = 0; i < 8; ++i) v[i] = row[(int64_t)i * plane + col];
@@ -702,7 +702,7 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
                     march_gather<0>(cur, mid[s - 1], up2[s - 1], g);
                 }
                 if (s < K) {
-                    const int gy = wrapm(yi - s, ny, kMarchRows + 2 * K + PF);
+                    const int gy = wrapm(yi - s, ny, a.march_rows + 2 * K + PF);
                     if (s == 1 && a.apply_shift) {
                         // the empty asm keeps this a branch: as selects the
                         // shift would run on every row of every lattice

@@ -140,18 +140,22 @@ enum FusedEnd { kEndPlain = 0, kEndSnap = 1, kEndCheck = 2, kEndMoments = 3 };
 // Fused kernel (several time steps per pass over HBM, temporal blocking): a
 // wavefront takes a strip of fused_width output columns (a window of 64
 // columns with a halo of fuse_max nodes on each side) of a chunk of
-// kMarchRows rows, and marches along y advancing up to fuse_max steps; see the
+// march_rows rows, and marches along y advancing up to fuse_max steps; see the
 // device file.  The kernel is bound by vector ALU issue, not by HBM (with six
 // steps per launch an FP32 update moves about a fifth of the single-step
 // bytes), so the most steps per launch is a per-kind balance between the HBM
 // bytes saved, the halo nodes recomputed and the registers the delay lines
-// take (FP32: 88 / 102 / 116 / 130 VGPRs at 4 / 5 / 6 / 7 steps).  For the
+// take (FP32: 62 / 67 / 82 / 95 VGPRs at 4 / 5 / 6 / 7 steps, and 24 KB of LDS
+// per block).  For the
 // 16-bit kinds it also depends on how many of a launch's steps are rounded to
 // the storage type (FusedRounding): rounding every step, four steps per
 // launch were the fastest (FP16-SR 743, F16_SPLIT 819 us per launch on
-// 8192^2); rounding the last one, six.  Chunks of 64 or 128 rows instead of
-// 32: FP32 302 / 289 GLUPS at six steps against 315.
+// 8192^2); rounding the last one, six.  Chunks of kMarchRows rows, or kTallRows
+// in large 16-bit handles (march_rows_of).
 constexpr int kMarchRows = 32;
+constexpr int kTallRows = 64;
+// Three rounds of strips at five wavefronts per SIMD.
+constexpr int64_t kTallStrips = 3 * 256 * 4 * 5;
 // Elements between direction runs in the chunked layout (64-node segments).
 constexpr int kChunkPlane = 64;
 __host__ __device__ constexpr int fuse_max(int storage) {
@@ -187,6 +191,7 @@ struct StepArgs {
     uint32_t* ctr_out;          // written with ctr_in + steps by the launch's first tile
     uint32_t seed;              // stream of the stochastic-rounding bits
     int32_t sr;                 // 1: round stores stochastically (nodes per lane must be 1)
+    int32_t march_rows = kMarchRows;   // fused kernel: output rows per strip
     // kEndMoments: the moments of instance out_inst also go to the caller's
     // FP64 arrays (ny nx each; null: not wanted)
     int32_t out_inst = -1;

@@ -104,8 +104,10 @@ Geometry geometry_of(const lbm_instance& in, int es, int layout, bool split = fa
 // whatever the number of stages; below five FP32 steps it is bound by memory
 // requests, above by VALU issue), so the way a short run is cut into launches
 // matters: 20 FP32 steps cost 3522 us as 7 + 7 + 6 and 4372 us as 5 + 5 + 5 +
-// 5.  The check variants of five, six and seven FP32 steps need 131, 145 and
-// 159 VGPRs (three waves per SIMD instead of four).  16-bit kinds: rounding
+// 5.  (Check variants: 97 .. 128 VGPRs at four to seven FP32 steps, four waves
+// per SIMD, against five of the plain ones.)  The figures were taken with all
+// delay lines in registers; only their ratios are used, and changing those of
+// the 16-bit kinds would change where their runs round.  16-bit kinds: rounding
 // every step (every_step) or only the last of a launch (FusedRounding).
 // lbm_autotune replaces the plain figures by its own timings on the handle's
 // lattices and scales the check figures.
@@ -236,6 +238,22 @@ int64_t max_tiles(const std::vector<lbm_instance>& v) {
 // Two-step kernel tiles along x of one instance.
 int64_t fused_tiles_x(const lbm_instance& in, int storage) {
     return (in.nx + fused_width(storage) - 1) / fused_width(storage);
+}
+
+// Rows per strip of the fused kernel: kTallRows for 16-bit storage (rounding
+// the last step) where that leaves kTallStrips strips, else kMarchRows.  Taller
+// chunks recompute fewer rows, but their launches end on longer strips, so they
+// need several rounds of them.  Measured (us per step, 32 / 64 rows; rounds of
+// 64-row strips): FP16-SR 8192^2 148.5 / 144.6 (4.0), 3000 x 20000 134.0 / 130.3
+// (3.5), F16_SPLIT 16384^2 598 / 560 (15.8; 128 rows 555); on the other side
+// 5000 x 7000 81.0 / 83.8 (2.1), 4096^2 40.6 / 40.0 (1.0), 3000 x 2500 21.4 /
+// 28.0.  FP32, bound by its requests to HBM, runs slower with them everywhere
+// (48 rows, 8192^2: 183 / 194), 24 rows 184.
+int march_rows_of(const std::vector<lbm_instance>& v, int storage, int every_step) {
+    if (storage == LBM_F32 || every_step) return kMarchRows;
+    int64_t strips = 0;
+    for (auto& in : v) strips += fused_tiles_x(in, storage) * (int64_t)((in.ny + kTallRows - 1) / kTallRows);
+    return strips >= kTallStrips ? kTallRows : kMarchRows;
 }
 
 // Block-kernel tiles along x and y of one instance.
@@ -383,7 +401,7 @@ Layout layout_of(const std::vector<lbm_instance>& v, int storage, int check, int
     L.buf_bytes = align_up(elems * es, kAlign);
     L.tiles_max = max_tiles(v);
     L.groups_max = max_groups(v);
-    const int ph = kMarchRows;
+    const int ph = kMarchRows;   // taller chunks need fewer strips
     for (auto& in : v) {
         const int64_t pt = fused_tiles_x(in, storage) * (int64_t)((in.ny + ph - 1) / ph);
         L.ptiles += pt;
@@ -453,6 +471,7 @@ struct lbm_ctx {
     std::vector<int32_t> ptile_inst;   // fused kernel: tile -> instance
     std::vector<int32_t> pgroup_inst;  // fused kernel: reduction group -> instance
     int64_t npgroups = 0;
+    int march_rows = kMarchRows;       // fused kernel: output rows per strip
     BlockPlan bplan;                   // block kernels (kBlockNone: not for these instances)
     bool block_on = false;             // single steps run in the block kernels (see plan_block)
     std::vector<int32_t> btile_inst;   // block kernels: tile -> instance
@@ -603,7 +622,7 @@ static void build_tiles(lbm_ctx* h) {
         h->group_inst.insert(h->group_inst.end(), (size_t)d.ngroups, (int32_t)k);
         d.p_tiles_x = (int32_t)fused_tiles_x(h->inst[k], h->storage);
         d.p_tile_begin = (int32_t)h->ptile_inst.size();
-        d.p_ntiles = d.p_tiles_x * ((d.ny + kMarchRows - 1) / kMarchRows);
+        d.p_ntiles = d.p_tiles_x * ((d.ny + h->march_rows - 1) / h->march_rows);
         h->ptile_inst.insert(h->ptile_inst.end(), (size_t)d.p_ntiles, (int32_t)k);
         d.p_group_begin = (int32_t)h->npgroups;
         d.p_ngroups = (d.p_ntiles + kGroup - 1) / kGroup;
@@ -971,6 +990,7 @@ int lbm_create(const lbm_config* cfg, lbm_handle* out) {
     h->shape.xcd = 1;
     h->shape.nt = 0;
     h->bplan = block_plan(v, h->storage);
+    h->march_rows = march_rows_of(v, h->storage, h->every_step);
     build_tiles(h);
     // steps per launch: the kind's most when the instances hold enough strips
     // of the fused kernel to fill the chip, else single steps.  Measured on
@@ -978,7 +998,8 @@ int lbm_create(const lbm_config* cfg, lbm_handle* out) {
     // 1024^2 10.3 / 12.6 (640 strips), 2048 x 1024 17.7 / 14.4 (1280 strips),
     // 8192^2 741 / 213: a fused launch takes about one strip's marching time
     // however few strips there are.
-    h->fuse = (int64_t)h->ptile_inst.size() >= kFuseMinStrips ? h->fuse_cap() : 1;
+    // (Counted in strips of kMarchRows rows.)
+    h->fuse = h->L.ptiles >= kFuseMinStrips ? h->fuse_cap() : 1;
     // steps in the block kernels (the same bits as single steps) where their
     // plan fits, unless fused launches keep 16-bit states in FP32
     h->block_on = h->bplan.kind != kBlockNone && (h->fuse == 1 || h->every_step);
@@ -1295,6 +1316,7 @@ static int issue_fused(lbm_ctx* h, int64_t m, int nsteps, int end, int src_k, hi
     StepArgs a;
     a.desc = h->d_desc();
     a.tile_inst = h->d_ptiles();
+    a.march_rows = h->march_rows;
     a.src = h->buf(src_k);
     a.dst = h->buf(1 - src_k);
     a.snap = h->d_snap();
@@ -1590,11 +1612,13 @@ static int replay_tail(lbm_ctx* h, int32_t k = -1, double* const* out = nullptr)
     if (!h->every_step) {
         a.snap = reinterpret_cast<double*>(h->buf(lbm_ctx::kReadout));
         a.tile_inst = h->d_ptiles();
+        a.march_rows = h->march_rows;
         a.ntiles = (int32_t)h->ptile_inst.size();
         HIPCALL(h, launch_fused(h->storage, h->shape, a, t.k, kEndMoments, h->layout == LBM_LAYOUT_CHUNKED,
                                 kRoundLast, h->L.nodes, h->stream));
     } else if (t.k - 1 >= 2) {
         a.tile_inst = h->d_ptiles();
+        a.march_rows = h->march_rows;
         a.ntiles = (int32_t)h->ptile_inst.size();
         HIPCALL(h, launch_fused(h->storage, h->shape, a, t.k - 1, kEndPlain, h->layout == LBM_LAYOUT_CHUNKED,
                                 kRoundEvery, h->L.nodes, h->stream));
@@ -1962,6 +1986,7 @@ static int time_fused(lbm_ctx* h, int k, int launches, hipEvent_t e0, hipEvent_t
     StepArgs a;
     a.desc = h->d_desc();
     a.tile_inst = h->d_ptiles();
+    a.march_rows = h->march_rows;
     a.snap = nullptr;
     a.partials = nullptr;
     a.tile_base = 0;

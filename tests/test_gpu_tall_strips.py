@@ -1,0 +1,35 @@
+"""Large 16-bit handles march strips of 64 rows instead of 32: the split of the
+work changes no field bits.  A lattice of many strips whose field repeats along
+y must stay equal, period by period, to one period of it."""
+import pytest
+import torch
+
+import workloads as W
+from paper_2010_01847_amd import Lattice, instance_from_case
+from parity_util import log
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16", "f16_split"])
+@pytest.mark.parametrize("kw", [{}, dict(bc_x="isothermal", t_wall=(1.004, 0.997, 0, 0))])
+def test_periods_of_a_tall_lattice(storage, kw):
+    # 2 strips x 7688 chunks of 64 rows (the last one half full); one period of
+    # 1000 rows ends inside a chunk of either kind
+    nx, ny, m = 59, 1000, 492
+    T = torch.from_numpy(W.random_field(nx, ny, 1e-3, 1.0, 7)).cuda()
+    got = []
+    for reps in (1, m):
+        c = W.Case("tall", nx, ny * reps, 0.6, 7.0, **kw)
+        lat = Lattice([instance_from_case(c, 2.0 ** -19)], storage=storage, check_interval=0)
+        lat.set_step_fusion(6)
+        lat.init(0, T.repeat(reps, 1))
+        out = []
+        for n in (6, 5, 13, 2):
+            lat.step(n)
+            out.append([t.view(reps, ny, nx) for t in lat.moments_device(0)])
+        lat.close()
+        got.append(out)
+    for one, many in zip(*got):
+        assert all(torch.equal(a.expand_as(b), b) for a, b in zip(one, many))
+    log(f"{m} periods in {storage}: equal to one")
