@@ -166,7 +166,8 @@ int lbm3d_get_launch_shape(lbm3d_handle h, lbm3d_launch_shape* shape);
  * overwrites the buffers).  report, if not NULL, receives a JSON summary
  * ({"timings_us": [[rows, xcd, nt, tile_waves, us], ...], "best": [rows, xcd,
  * nt, tile_waves, single-step us], "pair_us_per_step": [[zchunk, nt, us],
- * ...], "zchunk": z, "steps_per_launch": 1 or 2}) truncated to report_len.
+ * ...], "zchunk": z, "steps_per_launch": 1 or 2, "launch_steps": 1, 2 or 3
+ * (the steps its launches take)}) truncated to report_len.
  * Errors: ESTATE (memory not bound, or already initialised), EHIP. */
 int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_len);
 

@@ -657,7 +657,8 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
              best.xcd_remap, best.nontemporal, best.tile_waves, single_us);
     rep += b;
     rep += prep;
-    snprintf(b, sizeof b, "], \"zchunk\": %d, \"steps_per_launch\": %d}", best.zchunk, h->fuse);
+    snprintf(b, sizeof b, "], \"zchunk\": %d, \"steps_per_launch\": %d, \"launch_steps\": %d}", best.zchunk, h->fuse,
+             h->deep() ? kDeepSteps : h->fuse);
     rep += b;
     if (report && report_len) {
         strncpy(report, rep.c_str(), report_len - 1);
