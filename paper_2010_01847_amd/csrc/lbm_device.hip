@@ -563,28 +563,40 @@ hipError_t launch_plane_moments(const InstDesc* d_desc, int inst, const InstDesc
 // CH: chunked layout, whose direction runs are kChunkPlane elements apart, so
 // that the eight loads or stores of a row share one address and differ by
 // immediate offsets.
-// The first kDelayLevels levels keep their c_y = +1 movers (two rows of three
-// values) in LDS, 1.5 KB per level and wavefront, the others in registers.  The
-// kernel is bound by VALU issue, which more wavefronts per SIMD fill better:
-// 90-96 VGPRs instead of 114-128 allow five instead of four, whose LDS (120 KB
-// of a CU's 160) four levels leave room for.  Reading a level back at the
-// neighbouring lanes' addresses also saves its two diagonal DPP pulls and six
-// moves.  Measured (8192^2, us per step, all in registers / this): FP16-SR
-// 159.5 / 145.6, FP16 154.6 / 139.6, BF16-SR 163 / 156, F16_SPLIT 167 / 153,
-// BF16_SPLIT 168 / 154, FP32 179.4 / 177.2 (bound by its HBM traffic there;
-// 3000 x 2500: 27.3 / 23.9).  At four wavefronts per SIMD the LDS form is 2%
-// slower than registers; five levels leave LDS for four (FP16-SR 164); all
-// five delayed movers of three levels 145.7, of two 163 (105 VGPRs).
+// In launches of many steps the first kDelayLevels levels keep their c_y = +1
+// movers (two rows of three values) in LDS, 1.5 KB per level and wavefront, the
+// others in registers.  These launches are bound by VALU issue, which more
+// wavefronts per SIMD fill better: 90-96 VGPRs instead of 114-128 allow five
+// instead of four, whose LDS (120 KB of a CU's 160) four levels leave room for.
+// Reading a level back at the neighbouring lanes' addresses also saves its two
+// diagonal DPP pulls and six moves.  Measured (8192^2, us per step, all in
+// registers / this): FP16-SR 159.5 / 145.6, FP16 154.6 / 139.6, BF16-SR 163 /
+// 156, F16_SPLIT 167 / 153, BF16_SPLIT 168 / 154, FP32 179.4 / 177.2 (bound by
+// its HBM traffic there; 3000 x 2500: 27.3 / 23.9).  At four wavefronts per SIMD
+// the LDS form is 2% slower than registers; five levels leave LDS for four
+// (FP16-SR 164); all five delayed movers of three levels 145.7, of two 163 (105
+// VGPRs).
+// Launches of fewer steps wait for memory, and more wavefronts in flight or LDS
+// in their chain only cost: registers / LDS, us per step as a call of that many
+// steps, FP32 two steps 608 / 652, four 308 / 326, five 219 / 267, six 202 / 201;
+// FP16-SR two 289 / 347, four on 3000 x 2500 22.0 / 24.8, five 171 / 159;
+// F16_SPLIT four 198 / 221, five 190 / 177; rounding every step, FP16-SR four on
+// 3000 x 2500 30.7 / 34.0.  So FP32 takes it from seven steps on, 16-bit storage
+// from five.  Launches ending on a check step (four wavefronts per SIMD instead
+// of three): FP16-SR six steps 8192^2 211 / 180, 3000 x 2500 30.8 / 32.0; FP32
+// to nearest, seven, 232 / 224 and 32.4 / 35.6, so in registers; FP32-SR 538 /
+// 465 and 76.7 / 75.3.
 constexpr int kDelayLevels = 4;
-// Waves per SIMD the register allocation must leave room for (1: no
-// constraint).
-template <int END>
-struct MarchWaves {
-    static constexpr int value = END == kEndPlain ? 5 : 1;
+template <class S, int SR, int K, int END>
+struct MarchForm {
+    static constexpr bool lds = sizeof(S) == 4 ? K >= 7 && (SR || END == kEndPlain) : K >= 5;
+    static constexpr int levels = lds ? kDelayLevels : 0;
+    // waves per SIMD the register allocation must leave room for (1: no constraint)
+    static constexpr int waves = levels && END == kEndPlain ? 5 : 1;
 };
 
 template <class S, int SR, int SPLIT, int K, int KMAX, int END, int CH, int RM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MarchWaves<END>::value)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MarchForm<S, SR, K, END>::waves)))
 void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     static_assert(K >= 2 && K <= KMAX, "stages per launch");
     static_assert(RM == kRoundEvery || sizeof(S) == 2, "FP32 storage rounds every step");
@@ -647,8 +659,8 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     // (levels below DL keep the c_y = +1 movers in LDS, in the slots of the
     // last two rows; `par`: the slot this iteration reads and refills.  A
     // wavefront touches its own part only, in program order: no barrier.)
-    constexpr int DL = K < kDelayLevels ? K : kDelayLevels;
-    __shared__ float delay[4][DL][2][3][64];
+    constexpr int DL = MarchForm<S, SR, K, END>::levels;
+    __shared__ float delay[4][DL ? DL : 1][2][3][64];
     const uint32_t mine = (threadIdx.x >> 6) * (uint32_t)sizeof(delay[0]);
     const uint32_t at_c = mine + (uint32_t)lane * 4u, at_l = mine + (uint32_t)((lane - 1) & 63) * 4u,
                    at_r = mine + (uint32_t)((lane + 1) & 63) * 4u;

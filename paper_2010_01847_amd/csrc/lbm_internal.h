@@ -153,7 +153,7 @@ enum FusedEnd { kEndPlain = 0, kEndSnap = 1, kEndCheck = 2, kEndMoments = 3 };
 // 8192^2); rounding the last one, six.  Chunks of kMarchRows rows, or kTallRows
 // in large 16-bit handles (march_rows_of).
 constexpr int kMarchRows = 32;
-constexpr int kTallRows = 64;
+constexpr int kTallRows = 64, kTallSteps = 5;
 // Three rounds of strips at five wavefronts per SIMD.
 constexpr int64_t kTallStrips = 3 * 256 * 4 * 5;
 // Elements between direction runs in the chunked layout (64-node segments).

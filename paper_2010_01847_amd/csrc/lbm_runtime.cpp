@@ -247,7 +247,9 @@ int64_t fused_tiles_x(const lbm_instance& in, int storage) {
 // 64-row strips): FP16-SR 8192^2 148.5 / 144.6 (4.0), 3000 x 20000 134.0 / 130.3
 // (3.5), F16_SPLIT 16384^2 598 / 560 (15.8; 128 rows 555); on the other side
 // 5000 x 7000 81.0 / 83.8 (2.1), 4096^2 40.6 / 40.0 (1.0), 3000 x 2500 21.4 /
-// 28.0.  FP32, bound by its requests to HBM, runs slower with them everywhere
+// 28.0.  Launches of fewer steps wait for memory and share rows in the caches
+// better with short strips (8192^2, F16_SPLIT: two steps 364 / 400, four 198 /
+// 206), so handles set to fewer than kTallSteps keep 32.  FP32, bound by its requests to HBM, runs slower with them everywhere
 // (48 rows, 8192^2: 183 / 194), 24 rows 184.
 int march_rows_of(const std::vector<lbm_instance>& v, int storage, int every_step) {
     if (storage == LBM_F32 || every_step) return kMarchRows;
@@ -1828,7 +1830,11 @@ int lbm_set_step_fusion(lbm_handle h, int32_t steps) {
     h->fuse = steps;
     h->block_on = false;
     h->drop_graphs();
-    return LBM_OK;
+    const int rows = steps >= kTallSteps ? march_rows_of(h->inst, h->storage, h->every_step) : kMarchRows;
+    if (rows == h->march_rows) return LBM_OK;
+    h->march_rows = rows;
+    build_tiles(h);
+    return h->base ? upload_tables(h) : LBM_OK;
 }
 
 int32_t lbm_get_step_fusion(lbm_handle h) { return valid(h) ? h->fuse : -1; }

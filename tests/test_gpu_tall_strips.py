@@ -33,3 +33,27 @@ def test_periods_of_a_tall_lattice(storage, kw):
     for one, many in zip(*got):
         assert all(torch.equal(a.expand_as(b), b) for a, b in zip(one, many))
     log(f"{m} periods in {storage}: equal to one")
+
+
+@pytest.mark.parametrize("order", [(6, 2, 6), (3, 6, 4)])
+def test_changing_the_steps_per_launch(order):
+    # fewer steps per launch go back to strips of 32 rows, between calls and
+    # with a readout of the launch before pending; rounding to nearest, FP32
+    # between, so a run is fixed by its launches alone
+    nx, ny, m = 59, 1000, 492
+    T = torch.from_numpy(W.random_field(nx, ny, 1e-3, 1.0, 8)).cuda()
+    got = []
+    for reps in (1, m):
+        lat = Lattice([instance_from_case(W.Case("tall", nx, ny * reps, 0.6, 7.0), 2.0 ** -19)], storage="f16",
+                      check_interval=0)
+        lat.init(0, T.repeat(reps, 1))
+        out = []
+        for k in order:
+            lat.set_step_fusion(k)
+            lat.step(12)
+            lat.set_step_fusion(5)
+            out.append([t.view(reps, ny, nx) for t in lat.moments_device(0)])
+        lat.close()
+        got.append(out)
+    for one, many in zip(*got):
+        assert all(torch.equal(a.expand_as(b), b) for a, b in zip(one, many))
