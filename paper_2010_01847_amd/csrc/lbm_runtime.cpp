@@ -251,11 +251,17 @@ int64_t fused_tiles_x(const lbm_instance& in, int storage) {
 // better with short strips (8192^2, F16_SPLIT: two steps 364 / 400, four 198 /
 // 206), so handles set to fewer than kTallSteps keep 32.  FP32, bound by its requests to HBM, runs slower with them everywhere
 // (48 rows, 8192^2: 183 / 194), 24 rows 184.
+// kShortRows where their strips are at most kShortStrips: a launch then lasts as
+// long as one strip, and up to three wavefronts per SIMD hardly slow each other.
+int64_t strips_of(const std::vector<lbm_instance>& v, int storage, int rows) {
+    int64_t n = 0;
+    for (auto& in : v) n += fused_tiles_x(in, storage) * (int64_t)((in.ny + rows - 1) / rows);
+    return n;
+}
 int march_rows_of(const std::vector<lbm_instance>& v, int storage, int every_step) {
     if (storage == LBM_F32 || every_step) return kMarchRows;
-    int64_t strips = 0;
-    for (auto& in : v) strips += fused_tiles_x(in, storage) * (int64_t)((in.ny + kTallRows - 1) / kTallRows);
-    return strips >= kTallStrips ? kTallRows : kMarchRows;
+    if (strips_of(v, storage, kShortRows) <= kShortStrips) return kShortRows;
+    return strips_of(v, storage, kTallRows) >= kTallStrips ? kTallRows : kMarchRows;
 }
 
 // Block-kernel tiles along x and y of one instance.
@@ -379,6 +385,7 @@ struct Layout {
     size_t off_snap = 0, off_part = 0, off_res = 0, off_mpart = 0, off_mres = 0, off_desc = 0,
            off_desc_prev = 0, off_ref = 0, off_ref_prev = 0, off_tiles = 0, off_ptiles = 0, off_groups = 0,
            off_pgroups = 0, off_btiles = 0, off_bgroups = 0, off_gpart = 0, off_ctr = 0, total = 0;
+    int64_t strips = 0;      // fused-kernel strips of kMarchRows rows
     int64_t nodes = 0, tiles_max = 0, mparts_max = 0, groups_max = 0, ptiles = 0, pgroups = 0, btiles = 0,
             bgroups = 0;
 };
@@ -403,7 +410,9 @@ Layout layout_of(const std::vector<lbm_instance>& v, int storage, int check, int
     L.buf_bytes = align_up(elems * es, kAlign);
     L.tiles_max = max_tiles(v);
     L.groups_max = max_groups(v);
-    const int ph = kMarchRows;   // taller chunks need fewer strips
+    // tables for the most strips that a handle may use (see march_rows_of)
+    L.strips = strips_of(v, storage, kMarchRows);
+    const int ph = std::min(kMarchRows, march_rows_of(v, storage, every_step));
     for (auto& in : v) {
         const int64_t pt = fused_tiles_x(in, storage) * (int64_t)((in.ny + ph - 1) / ph);
         L.ptiles += pt;
@@ -1001,7 +1010,7 @@ int lbm_create(const lbm_config* cfg, lbm_handle* out) {
     // 8192^2 741 / 213: a fused launch takes about one strip's marching time
     // however few strips there are.
     // (Counted in strips of kMarchRows rows.)
-    h->fuse = h->L.ptiles >= kFuseMinStrips ? h->fuse_cap() : 1;
+    h->fuse = h->L.strips >= kFuseMinStrips ? h->fuse_cap() : 1;
     // steps in the block kernels (the same bits as single steps) where their
     // plan fits, unless fused launches keep 16-bit states in FP32
     h->block_on = h->bplan.kind != kBlockNone && (h->fuse == 1 || h->every_step);

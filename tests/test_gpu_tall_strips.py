@@ -1,5 +1,5 @@
-"""Large 16-bit handles march strips of 64 rows instead of 32: the split of the
-work changes no field bits.  A lattice of many strips whose field repeats along
+"""Large 16-bit handles march strips of 64 rows instead of 32, small ones of 16:
+the split of the work changes no field bits.  A lattice of many strips whose field repeats along
 y must stay equal, period by period, to one period of it."""
 import pytest
 import torch
@@ -19,7 +19,7 @@ def test_periods_of_a_tall_lattice(storage, kw):
     nx, ny, m = 59, 1000, 492
     T = torch.from_numpy(W.random_field(nx, ny, 1e-3, 1.0, 7)).cuda()
     got = []
-    for reps in (1, m):
+    for reps in (1, 24, 30, m):     # 126, 3000 and 3750 strips of 16 rows: 16, 16 and 32 rows
         c = W.Case("tall", nx, ny * reps, 0.6, 7.0, **kw)
         lat = Lattice([instance_from_case(c, 2.0 ** -19)], storage=storage, check_interval=0)
         lat.set_step_fusion(6)
@@ -30,8 +30,9 @@ def test_periods_of_a_tall_lattice(storage, kw):
             out.append([t.view(reps, ny, nx) for t in lat.moments_device(0)])
         lat.close()
         got.append(out)
-    for one, many in zip(*got):
-        assert all(torch.equal(a.expand_as(b), b) for a, b in zip(one, many))
+    for other in got[1:]:
+        for one, many in zip(got[0], other):
+            assert all(torch.equal(a.expand_as(b), b) for a, b in zip(one, many))
     log(f"{m} periods in {storage}: equal to one")
 
 
