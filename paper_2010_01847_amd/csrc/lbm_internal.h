@@ -154,8 +154,8 @@ enum FusedEnd { kEndPlain = 0, kEndSnap = 1, kEndCheck = 2, kEndMoments = 3 };
 // or kShortRows in large and small 16-bit handles (march_rows_of).
 constexpr int kMarchRows = 32;
 constexpr int kTallRows = 64, kTallSteps = 5, kShortRows = 16;
-// Three wavefronts per SIMD.
-constexpr int64_t kShortStrips = 3 * 1024;
+// One round of strips.
+constexpr int64_t kShortStrips = 256 * 4 * 5;
 // Three rounds of strips at five wavefronts per SIMD.
 constexpr int64_t kTallStrips = 3 * 256 * 4 * 5;
 // Elements between direction runs in the chunked layout (64-node segments).

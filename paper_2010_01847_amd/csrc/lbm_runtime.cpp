@@ -251,8 +251,10 @@ int64_t fused_tiles_x(const lbm_instance& in, int storage) {
 // better with short strips (8192^2, F16_SPLIT: two steps 364 / 400, four 198 /
 // 206), so handles set to fewer than kTallSteps keep 32.  FP32, bound by its requests to HBM, runs slower with them everywhere
 // (48 rows, 8192^2: 183 / 194), 24 rows 184.
-// kShortRows where their strips are at most kShortStrips: a launch then lasts as
-// long as one strip, and up to three wavefronts per SIMD hardly slow each other.
+// kShortRows where their strips fit in one round (kShortStrips): a launch then
+// lasts as long as one strip.  FP16-SR, us per step, 32 / 16 rows: 1200 x 1400
+// (2112 strips of 16 rows) 12.8 / 9.3, 1800 x 1600 (3500) 13.0 / 10.9, 4000 x 900
+// (4389) 15.4 / 12.5, on the other side 2200 x 2000 (5375) 15.5 / 15.6.
 int64_t strips_of(const std::vector<lbm_instance>& v, int storage, int rows) {
     int64_t n = 0;
     for (auto& in : v) n += fused_tiles_x(in, storage) * (int64_t)((in.ny + rows - 1) / rows);

@@ -19,7 +19,7 @@ def test_periods_of_a_tall_lattice(storage, kw):
     nx, ny, m = 59, 1000, 492
     T = torch.from_numpy(W.random_field(nx, ny, 1e-3, 1.0, 7)).cuda()
     got = []
-    for reps in (1, 24, 30, m):     # 126, 3000 and 3750 strips of 16 rows: 16, 16 and 32 rows
+    for reps in (1, 40, 44, m):     # 126, 5000 and 5500 strips of 16 rows: 16, 16 and 32 rows
         c = W.Case("tall", nx, ny * reps, 0.6, 7.0, **kw)
         lat = Lattice([instance_from_case(c, 2.0 ** -19)], storage=storage, check_interval=0)
         lat.set_step_fusion(6)
