@@ -390,6 +390,9 @@ struct Layout {
     int64_t strips = 0;      // fused-kernel strips of kMarchRows rows
     int64_t nodes = 0, tiles_max = 0, mparts_max = 0, groups_max = 0, ptiles = 0, pgroups = 0, btiles = 0,
             bgroups = 0;
+    // first check record and first first-stage record of single steps (0),
+    // fused (1) and block (2) launches
+    int64_t rec0[3] = {0, 0, 0}, grec0[3] = {0, 0, 0};
 };
 
 // Fused launches round every step: FP32 storage, or LBM_FLAG_ROUND_EVERY_STEP.
@@ -427,11 +430,20 @@ Layout layout_of(const std::vector<lbm_instance>& v, int storage, int check, int
             L.btiles += bt;
             L.bgroups += (bt + kGroup - 1) / kGroup;
         }
-    // check-step records: per single-step, fused-kernel or block-kernel tile
-    const int64_t records = std::max({L.tiles_max, L.ptiles, L.btiles});
-    // the same scratch serves the first stage of every check reduction and of
-    // lbm_totals' reduction
-    const int64_t gscratch = std::max({L.groups_max, L.pgroups, L.bgroups, (L.mparts_max + kGroup - 1) / kGroup});
+    // check-step records, per single-step, fused-kernel or block-kernel tile:
+    // each kind of launch has records of its own, because within one call the
+    // parts' streams (lbm_set_streams) are not ordered against each other, and
+    // one may still reduce the records of a single check step while the other
+    // writes those of a later fused or block launch.  Within a kind the tiles
+    // of different instances never share a record.
+    L.rec0[1] = L.tiles_max;
+    L.rec0[2] = L.rec0[1] + L.ptiles;
+    const int64_t records = L.rec0[2] + L.btiles;
+    // the first stage of the check reductions likewise; that of the single
+    // steps also serves lbm_totals' reduction (issued between calls)
+    L.grec0[1] = std::max(L.groups_max, (L.mparts_max + kGroup - 1) / kGroup);
+    L.grec0[2] = L.grec0[1] + L.pgroups;
+    const int64_t gscratch = L.grec0[2] + L.bgroups;
     size_t o = 0;
     L.off_buf[0] = o; o += L.buf_bytes;
     L.off_buf[1] = o; o += L.buf_bytes;
@@ -570,9 +582,12 @@ struct lbm_ctx {
     int32_t* d_btiles() const { return reinterpret_cast<int32_t*>(base + L.off_btiles); }
     int32_t* d_bgroups() const { return reinterpret_cast<int32_t*>(base + L.off_bgroups); }
     int32_t* d_groups() const { return reinterpret_cast<int32_t*>(base + L.off_groups); }
-    DD* d_gpart() const { return reinterpret_cast<DD*>(base + L.off_gpart); }
+    // first-stage and check records of a kind of launch (Layout::rec0)
+    DD* d_gpart(int kind = 0) const {
+        return reinterpret_cast<DD*>(base + L.off_gpart) + L.grec0[kind] * kPartials;
+    }
+    DD* d_part(int kind = 0) const { return reinterpret_cast<DD*>(base + L.off_part) + L.rec0[kind] * kPartials; }
     double* d_snap() const { return K ? reinterpret_cast<double*>(base + L.off_snap) : nullptr; }
-    DD* d_part() const { return reinterpret_cast<DD*>(base + L.off_part); }
     double* d_res() const { return reinterpret_cast<double*>(base + L.off_res); }
     DD* d_mpart() const { return reinterpret_cast<DD*>(base + L.off_mpart); }
     DD* d_mres() const { return reinterpret_cast<DD*>(base + L.off_mres); }
@@ -1333,7 +1348,7 @@ static int issue_fused(lbm_ctx* h, int64_t m, int nsteps, int end, int src_k, hi
     a.src = h->buf(src_k);
     a.dst = h->buf(1 - src_k);
     a.snap = h->d_snap();
-    a.partials = h->d_part();
+    a.partials = h->d_part(1);
     a.ctr_in = h->d_ctr() + sp.ctr + src_k;
     a.ctr_out = h->d_ctr() + sp.ctr + (1 - src_k);
     a.seed = h->seed;
@@ -1346,7 +1361,7 @@ static int issue_fused(lbm_ctx* h, int64_t m, int nsteps, int end, int src_k, hi
                             h->every_step ? kRoundEvery : kRoundLast, h->L.nodes, st));
     if (end == kEndCheck)
         HIPCALL(h, launch_finalize(h->d_desc(), h->d_pgroups(), sp.pg0, sp.png, h->d_ref(), h->d_ref_prev(), sp.i0,
-                                   sp.ni, h->d_part(), h->d_gpart(), h->d_res(), 1, st));
+                                   sp.ni, h->d_part(1), h->d_gpart(1), h->d_res(), 1, st));
     return LBM_OK;
 }
 
@@ -1389,7 +1404,7 @@ static int issue_block(lbm_ctx* h, int64_t m, int k, int end, int src_k, bool ke
     a.src = h->buf(src_k);
     a.dst = h->buf(1 - src_k);
     a.snap = nullptr;
-    a.partials = h->d_part();
+    a.partials = h->d_part(2);
     a.ctr_in = h->d_ctr() + sp.ctr + src_k;
     a.ctr_out = h->d_ctr() + sp.ctr + (1 - src_k);
     a.seed = h->seed;
@@ -1407,7 +1422,7 @@ static int issue_block(lbm_ctx* h, int64_t m, int k, int end, int src_k, bool ke
     HIPCALL(h, launch_block(h->storage, h->bplan, h->shape, b, end, st));
     if (end == kEndCheck)
         HIPCALL(h, launch_finalize(h->d_desc(), h->d_bgroups(), sp.bg0, sp.bng, h->d_ref(), h->d_ref_prev(), sp.i0,
-                                   sp.ni, h->d_part(), h->d_gpart(), h->d_res(), 2, st));
+                                   sp.ni, h->d_part(2), h->d_gpart(2), h->d_res(), 2, st));
     return LBM_OK;
 }
 

@@ -1,0 +1,162 @@
+// What the D2Q8 host runtime launches, recorded on a host without a GPU: the
+// runtime source is compiled in, the HIP calls and the kernel launchers are
+// replaced by recorders.  The first argument names the check.
+#include "hip_stub.h"
+#include "lbm_runtime.cpp"
+
+#include <functional>
+
+// ------------------------------------------------------------------ recorders
+
+struct Launch {
+    hipStream_t stream;
+    int kind;              // 0 single step, 1 fused, 2 block, 3 reduction
+    int steps, end, rows;  // end: FusedEnd; rows: of a fused strip
+    BlockPlan plan;
+    bool keep;             // a block launch that also stores the state of the step before its last
+    // check records [lo, hi) it writes (or reads: reductions), and the first-stage records of a reduction
+    const DD *lo, *hi, *glo, *ghi;
+};
+static std::vector<Launch> launches;
+static std::function<float(const Launch&)> cost_us;   // what the autotuner's events report
+static double clock_us = 0.0;
+
+static void note(Launch l) {
+    if (cost_us) clock_us += cost_us(l);
+    launches.push_back(l);
+}
+static void records(Launch* l, const StepArgs& a, bool check) {
+    l->lo = check ? a.partials + (int64_t)a.tile_base * kPartials : nullptr;
+    l->hi = check ? l->lo + (int64_t)a.ntiles * kPartials : nullptr;
+}
+
+namespace plbm {
+hipError_t launch_step(int, const Shape&, int mode, const StepArgs& a, int64_t, hipStream_t st) {
+    Launch l{st, 0, 1, mode == kCheck ? kEndCheck : mode == kSnap ? kEndSnap : kEndPlain};
+    records(&l, a, mode == kCheck);
+    note(l);
+    return hipSuccess;
+}
+hipError_t launch_fused(int, const Shape&, const StepArgs& a, int k, int end, int, int, int64_t, hipStream_t st) {
+    Launch l{st, 1, k, end, a.march_rows};
+    records(&l, a, end == kEndCheck);
+    note(l);
+    return hipSuccess;
+}
+hipError_t launch_block(int, const BlockPlan& p, const Shape&, const BlockArgs& b, int end, hipStream_t st) {
+    Launch l{st, 2, b.steps, end, 0, p, b.prev != nullptr};
+    records(&l, b.s, end == kEndCheck);
+    note(l);
+    return hipSuccess;
+}
+// first record and count of instance `d`'s tiles and groups of a kind
+static void tiles_of(const InstDesc& d, int kind, int64_t* t0, int64_t* nt) {
+    *t0 = kind == 2 ? d.b_tile_begin : kind ? d.p_tile_begin : d.tile_begin;
+    *nt = kind == 2 ? d.b_ntiles : kind ? d.p_ntiles : d.ntiles;
+}
+hipError_t launch_finalize(const InstDesc* d, const int32_t*, int g0, int ngroups, RefState*, RefState*, int i0,
+                           int ninst, const DD* partials, DD* gpart, double*, int fused, hipStream_t st) {
+    Launch l{st, 3, 0, kEndCheck};
+    int64_t a0, an, b0, bn;
+    tiles_of(d[i0], fused, &a0, &an);
+    tiles_of(d[i0 + ninst - 1], fused, &b0, &bn);
+    l.lo = partials + a0 * kPartials;
+    l.hi = partials + (b0 + bn) * kPartials;
+    if (ngroups > ninst) {
+        l.glo = gpart + (int64_t)g0 * kPartials;
+        l.ghi = l.glo + (int64_t)ngroups * kPartials;
+    }
+    note(l);
+    return hipSuccess;
+}
+hipError_t launch_moments(int, const InstDesc*, const RefState*, int, const InstDesc&, const void*, int, int, int,
+                          void*, void*, void*, double, double, DD*, hipStream_t) { return hipSuccess; }
+hipError_t launch_plane_moments(const InstDesc*, int, const InstDesc&, const double*, int64_t, int, void*, void*,
+                                void*, double, double, DD*, hipStream_t) { return hipSuccess; }
+hipError_t launch_init(int, const InitTables&, int, const InstDesc&, const RefState&, void*, void*, const double*,
+                       const double*, const double*, double, double, double, hipStream_t) { return hipSuccess; }
+hipError_t launch_finalize_range(const DD*, int, DD*, DD*, hipStream_t) { return hipSuccess; }
+hipError_t launch_copy_u32(uint32_t*, const uint32_t*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_set_float(float*, float, hipStream_t) { return hipSuccess; }
+hipError_t launch_fill(void*, size_t, uint32_t, hipStream_t) { return hipSuccess; }
+hipError_t preload_fused(int, int, int, int, hipStream_t) { return hipSuccess; }
+}
+
+static std::map<hipEvent_t, double> event_us;
+extern "C" hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
+
+// ------------------------------------------------------------------ handles
+
+static lbm_instance inst(int nx, int ny) {
+    lbm_instance in;
+    std::memset(&in, 0, sizeof in);
+    in.nx = nx;
+    in.ny = ny;
+    in.tau_n = 0.6;
+    in.tau_r = 5.0;
+    in.cv = 1.0;
+    in.t0 = 1.0;
+    in.scale = 1.0;
+    return in;
+}
+
+static lbm_handle make(const std::vector<lbm_instance>& v, int storage, int check, int flags = 0) {
+    lbm_config c;
+    std::memset(&c, 0, sizeof c);
+    c.n_instances = (int32_t)v.size();
+    c.storage = storage;
+    c.check_interval = check;
+    c.flags = flags;
+    c.inst = v.data();
+    lbm_handle h = nullptr;
+    expect(lbm_create(&c, &h) == LBM_OK, "create");
+    static const double field = 1.0;
+    for (size_t k = 0; h && k < v.size(); ++k) expect(lbm_init_device(h, (int32_t)k, &field, nullptr, nullptr) == LBM_OK, "init");
+    return h;
+}
+
+static bool meet(const DD* a0, const DD* a1, const DD* b0, const DD* b1) { return a0 && b0 && a0 < b1 && b0 < a1; }
+
+// Within one call, the launches of one part's stream must not write check
+// records that the other part's stream reads or writes: the streams are
+// ordered at the call's beginning and end only.
+static void streams() {
+    const std::vector<std::vector<lbm_instance>> sets = {
+        {inst(300, 200), inst(310, 150), inst(64, 64)},
+        {inst(20, 20), inst(31, 9), inst(25, 33), inst(5, 7)},
+        {inst(1500, 1100), inst(900, 1000)},
+        {inst(3000, 3000), inst(2500, 2000), inst(700, 90)},
+    };
+    for (auto& v : sets)
+        for (int storage : {LBM_F32, LBM_F16})
+            for (int check : {2, 5, 10}) {
+                lbm_handle h = make(v, storage, check);
+                for (int fuse : {0, 4, 2}) {
+                    if (fuse) expect(lbm_set_step_fusion(h, fuse) == LBM_OK, "step fusion");
+                    // calls that end before, on and after the snapshot step of a check step
+                    for (int n : {check - 1, 4 * check, check + 1, 1, 3 * check - 1}) {
+                        launches.clear();
+                        expect(lbm_step(h, n) == LBM_OK, "step");
+                        for (auto& a : launches)
+                            for (auto& b : launches)
+                                if (a.stream != b.stream &&
+                                    (meet(a.lo, a.hi, b.lo, b.hi) || meet(a.glo, a.ghi, b.glo, b.ghi))) {
+                                    std::printf("%zu instances, storage %d, check %d, steps per launch %d, call of %d\n",
+                                                v.size(), storage, check, fuse, n);
+                                    expect(false, "check records of the two streams overlap");
+                                    goto next;
+                                }
+                    }
+                }
+            next:
+                lbm_destroy(h);
+            }
+}
+
+int main(int argc, char** argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "streams") streams();
+    else expect(false, "unknown check");
+    std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
+    return failures ? 1 : 0;
+}

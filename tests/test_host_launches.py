@@ -1,0 +1,38 @@
+"""What the host runtime launches, on the CPU: the runtime sources are compiled
+with the HIP calls and the kernel launchers replaced by recorders
+(``tests/host``), so rules that no field value shows can be checked without a
+GPU (and before anything runs on one)."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HOST = os.path.join(ROOT, "tests", "host")
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    built = {}
+
+    def run(name, check):
+        if name not in built:
+            exe = str(tmp_path_factory.mktemp("host") / name)
+            cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+                   "-D__HIP_PLATFORM_AMD__", "-isystem", os.path.join(ROCM, "include"), "-I",
+                   os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2010_01847_amd", "csrc"), "-I", HOST,
+                   os.path.join(HOST, name + ".cpp"), "-o", exe]
+            r = subprocess.run(cmd, capture_output=True, text=True)
+            assert r.returncode == 0, r.stderr[-4000:]
+            built[name] = exe
+        r = subprocess.run([built[name], check], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0 and f"{check}: ok" in r.stdout, r.stdout + r.stderr
+
+    return run
+
+
+def test_streams_share_no_check_records(driver):
+    """Two streams of one call, a lone check step before block or fused check
+    launches among the calls: neither writes records the other uses."""
+    driver("lattice_launches", "streams")
