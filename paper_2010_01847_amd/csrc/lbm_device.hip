@@ -658,7 +658,11 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     // the previous row and the c_y = +1 movers of the two previous rows
     // (levels below DL keep the c_y = +1 movers in LDS, in the slots of the
     // last two rows; `par`: the slot this iteration reads and refills.  A
-    // wavefront touches its own part only, in program order: no barrier.)
+    // wavefront touches its own part only, and the hardware keeps the order of
+    // its LDS accesses, so no barrier between wavefronts is needed; lane_order
+    // before every refill keeps the compiler to that order: the lanes' reads of
+    // their neighbours' values before the refill of the slot, and the refill
+    // before the reads two iterations later.)
     constexpr int DL = MarchForm<S, SR, K, END>::levels;
     __shared__ float delay[4][DL ? DL : 1][2][3][64];
     const uint32_t mine = (threadIdx.x >> 6) * (uint32_t)sizeof(delay[0]);
@@ -795,6 +799,7 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
             }
             // level s - 1 moves one row on (its values are valid whenever a later stage reads them)
             if (s - 1 < DL) {
+                lane_order();
                 const uint32_t o = (uint32_t)((s - 1) * sizeof(delay[0][0])) + par;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) delayed(at_c + o + 256 * k) = cur[yup(k)];
