@@ -620,13 +620,17 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     const int t = b * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (t >= a.ntiles) return;                // whole wavefront: no lane is left behind a DPP move
     const int tg = t + a.tile_base;
+    // halved (few-step launches of a handle with kTallRows strips): the launch's
+    // tiles are strips of half the table's height, two for each of the table's
+    constexpr bool HALVES = sizeof(S) == 2 && K < kTallSteps && END != kEndCheck;
+    const int halved = HALVES ? a.halved : 0;
     // a private copy of the descriptor, read once before the first store (the
     // compiler cannot keep fields of device memory in registers across stores)
-    const int inst = __builtin_amdgcn_readfirstlane(a.tile_inst[tg]);
+    const int inst = __builtin_amdgcn_readfirstlane(a.tile_inst[tg >> halved]);
     const InstDesc d = a.desc[inst];
     const RefView rv = ref_view(a.ref[inst]);
     const double q_ref = END != kEndPlain ? a.ref[inst].q_ref : 0.0;
-    const int local = tg - d.p_tile_begin;
+    const int local = tg - (d.p_tile_begin << halved);
     const int ty = local / d.p_tiles_x;
     const int tx = local - ty * d.p_tiles_x;
     // FP32 storage always takes kMarchRows, as a constant: with the count read
@@ -636,6 +640,7 @@ void march_kernel(StepArgs a, int xcd, int nontemporal, int64_t snap_stride) {
     const int rows = sizeof(S) == 4 ? kMarchRows : a.march_rows;
     const int x0 = tx * W, y0 = ty * rows;
     const int nx = d.nx, ny = d.ny;
+    if (HALVES && y0 >= ny) return;           // the last strip of the table may fill one half only
     const int gx = wrapm(x0 - KMAX + lane, nx, 64);
     const int iters = min(rows, ny - y0) + 2 * K;
     const uint32_t step = a.ctr_in[0];
@@ -970,6 +975,8 @@ static hipError_t launch_fused_s(const Shape& sh, const StepArgs& a, int k, int 
 hipError_t launch_fused(int storage, const Shape& sh, const StepArgs& a, int k, int end, int chunked,
                         int rounding, int64_t snap_stride, hipStream_t st) {
     if (a.ntiles <= 0) return hipSuccess;
+    if (a.halved && (storage == 0 || k >= kTallSteps || end == kEndCheck)) return hipErrorInvalidValue;
+    if (storage == 0 && a.march_rows != kMarchRows) return hipErrorInvalidValue;
     if ((end == kEndSnap || end == kEndMoments) && !a.snap) return hipErrorInvalidValue;
     if (end == kEndCheck && !a.partials) return hipErrorInvalidValue;
     if (end < kEndPlain || end > kEndMoments) return hipErrorInvalidValue;

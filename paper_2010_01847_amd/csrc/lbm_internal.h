@@ -193,7 +193,11 @@ struct StepArgs {
     uint32_t* ctr_out;          // written with ctr_in + steps by the launch's first tile
     uint32_t seed;              // stream of the stochastic-rounding bits
     int32_t sr;                 // 1: round stores stochastically (nodes per lane must be 1)
-    int32_t march_rows = kMarchRows;   // fused kernel: output rows per strip
+    int32_t march_rows = kMarchRows;   // fused kernel: output rows per strip of this launch
+    // fused kernel: 1 if the tile table's strips are twice that high (tile_base
+    // and ntiles count this launch's strips); 16-bit storage, fewer than
+    // kTallSteps steps, no check step
+    int32_t halved = 0;
     // kEndMoments: the moments of instance out_inst also go to the caller's
     // FP64 arrays (ny nx each; null: not wanted)
     int32_t out_inst = -1;

@@ -247,10 +247,11 @@ int64_t fused_tiles_x(const lbm_instance& in, int storage) {
 // 64-row strips): FP16-SR 8192^2 148.5 / 144.6 (4.0), 3000 x 20000 134.0 / 130.3
 // (3.5), F16_SPLIT 16384^2 598 / 560 (15.8; 128 rows 555); on the other side
 // 5000 x 7000 81.0 / 83.8 (2.1), 4096^2 40.6 / 40.0 (1.0), 3000 x 2500 21.4 /
-// 28.0.  Launches of fewer steps wait for memory and share rows in the caches
-// better with short strips (8192^2, F16_SPLIT: two steps 364 / 400, four 198 /
-// 206), so handles set to fewer than kTallSteps keep 32.  FP32, bound by its requests to HBM, runs slower with them everywhere
-// (48 rows, 8192^2: 183 / 194), 24 rows 184.
+// 28.0.  Launches of fewer than kTallSteps steps wait for memory and share rows
+// in the caches better with short strips (8192^2, F16_SPLIT: two steps 364 / 400,
+// four 198 / 206), so theirs are half as high (see strips_for).  FP32, bound by
+// its requests to HBM, runs slower with tall strips everywhere (48 rows, 8192^2:
+// 183 / 194), 24 rows 184.
 // kShortRows where their strips fit in one round (kShortStrips): a launch then
 // lasts as long as one strip.  FP16-SR, us per step, 32 / 16 rows: 1200 x 1400
 // (2112 strips of 16 rows) 12.8 / 9.3, 1800 x 1600 (3500) 13.0 / 10.9, 4000 x 900
@@ -415,9 +416,8 @@ Layout layout_of(const std::vector<lbm_instance>& v, int storage, int check, int
     L.buf_bytes = align_up(elems * es, kAlign);
     L.tiles_max = max_tiles(v);
     L.groups_max = max_groups(v);
-    // tables for the most strips that a handle may use (see march_rows_of)
     L.strips = strips_of(v, storage, kMarchRows);
-    const int ph = std::min(kMarchRows, march_rows_of(v, storage, every_step));
+    const int ph = march_rows_of(v, storage, every_step);
     for (auto& in : v) {
         const int64_t pt = fused_tiles_x(in, storage) * (int64_t)((in.ny + ph - 1) / ph);
         L.ptiles += pt;
@@ -1339,12 +1339,24 @@ static int plan_launch(const lbm_ctx* h, int64_t m, int64_t last, int* end) {
     return k;
 }
 
+// The strips of a launch of k steps over tiles t0 .. t0 + nt - 1 of the fused
+// tile table: of the table's height, or half of it where the table's strips are
+// tall and the launch takes few steps.  Launches that end on a check step keep
+// the table's: their records are per table entry, and they gain nothing from
+// lower strips (calls of 20 steps with a check step every four, 8192^2, 32 / 64
+// rows: FP16-SR 6012 / 5923 us, F16_SPLIT 6478 / 6439).
+static void strips_for(const lbm_ctx* h, int k, int end, int32_t t0, int32_t nt, StepArgs* a) {
+    a->halved = h->march_rows == kTallRows && k < kTallSteps && end != kEndCheck ? 1 : 0;
+    a->march_rows = h->march_rows >> a->halved;
+    a->tile_base = t0 << a->halved;
+    a->ntiles = nt << a->halved;
+}
+
 static int issue_fused(lbm_ctx* h, int64_t m, int nsteps, int end, int src_k, hipStream_t st,
                        const lbm_ctx::Span& sp) {
     StepArgs a;
     a.desc = h->d_desc();
     a.tile_inst = h->d_ptiles();
-    a.march_rows = h->march_rows;
     a.src = h->buf(src_k);
     a.dst = h->buf(1 - src_k);
     a.snap = h->d_snap();
@@ -1355,8 +1367,7 @@ static int issue_fused(lbm_ctx* h, int64_t m, int nsteps, int end, int src_k, hi
     a.sr = h->sr;
     a.ref = h->d_ref();
     a.apply_shift = (h->K > 0 && (m - 1) % h->K == 0) ? 1 : 0;
-    a.tile_base = sp.pt0;
-    a.ntiles = sp.pnt;
+    strips_for(h, nsteps, end, sp.pt0, sp.pnt, &a);
     HIPCALL(h, launch_fused(h->storage, h->shape, a, nsteps, end, h->layout == LBM_LAYOUT_CHUNKED,
                             h->every_step ? kRoundEvery : kRoundLast, h->L.nodes, st));
     if (end == kEndCheck)
@@ -1640,14 +1651,12 @@ static int replay_tail(lbm_ctx* h, int32_t k = -1, double* const* out = nullptr)
     if (!h->every_step) {
         a.snap = reinterpret_cast<double*>(h->buf(lbm_ctx::kReadout));
         a.tile_inst = h->d_ptiles();
-        a.march_rows = h->march_rows;
-        a.ntiles = (int32_t)h->ptile_inst.size();
+        strips_for(h, t.k, kEndMoments, 0, (int32_t)h->ptile_inst.size(), &a);
         HIPCALL(h, launch_fused(h->storage, h->shape, a, t.k, kEndMoments, h->layout == LBM_LAYOUT_CHUNKED,
                                 kRoundLast, h->L.nodes, h->stream));
     } else if (t.k - 1 >= 2) {
         a.tile_inst = h->d_ptiles();
-        a.march_rows = h->march_rows;
-        a.ntiles = (int32_t)h->ptile_inst.size();
+        strips_for(h, t.k - 1, kEndPlain, 0, (int32_t)h->ptile_inst.size(), &a);
         HIPCALL(h, launch_fused(h->storage, h->shape, a, t.k - 1, kEndPlain, h->layout == LBM_LAYOUT_CHUNKED,
                                 kRoundEvery, h->L.nodes, h->stream));
     } else {
@@ -1856,11 +1865,7 @@ int lbm_set_step_fusion(lbm_handle h, int32_t steps) {
     h->fuse = steps;
     h->block_on = false;
     h->drop_graphs();
-    const int rows = steps >= kTallSteps ? march_rows_of(h->inst, h->storage, h->every_step) : kMarchRows;
-    if (rows == h->march_rows) return LBM_OK;
-    h->march_rows = rows;
-    build_tiles(h);
-    return h->base ? upload_tables(h) : LBM_OK;
+    return LBM_OK;
 }
 
 int32_t lbm_get_step_fusion(lbm_handle h) { return valid(h) ? h->fuse : -1; }
@@ -2018,11 +2023,9 @@ static int time_fused(lbm_ctx* h, int k, int launches, hipEvent_t e0, hipEvent_t
     StepArgs a;
     a.desc = h->d_desc();
     a.tile_inst = h->d_ptiles();
-    a.march_rows = h->march_rows;
     a.snap = nullptr;
     a.partials = nullptr;
-    a.tile_base = 0;
-    a.ntiles = (int32_t)h->ptile_inst.size();
+    strips_for(h, k, kEndPlain, 0, (int32_t)h->ptile_inst.size(), &a);
     a.seed = h->seed;
     a.sr = h->sr;
     a.ref = h->d_ref();

@@ -26,6 +26,8 @@ namespace stub {
 static std::map<void*, size_t> blocks;
 static uintptr_t next_id = 1;
 static int host_allocs = 0;          // pinned allocations so far
+static double clock_us = 0.0;        // what events measure; the drivers advance it
+static std::map<hipEvent_t, double> event_us;
 template <class T> T id() { return reinterpret_cast<T>(next_id++); }
 }
 
@@ -67,7 +69,11 @@ hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { return *g = stub::i
 hipError_t hipEventCreate(hipEvent_t* e) { return *e = stub::id<hipEvent_t>(), hipSuccess; }
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { return stub::event_us[e] = stub::clock_us, hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+    *ms = (float)(1e-3 * (stub::event_us[b] - stub::event_us[a]));
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t, hipGraphNode_t*, char*, size_t) {
     return *x = stub::id<hipGraphExec_t>(), hipSuccess;

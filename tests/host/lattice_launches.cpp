@@ -11,18 +11,17 @@
 struct Launch {
     hipStream_t stream;
     int kind;              // 0 single step, 1 fused, 2 block, 3 reduction
-    int steps, end, rows;  // end: FusedEnd; rows: of a fused strip
+    int steps, end, rows, tiles;  // end: FusedEnd; rows, tiles: of a fused launch's strips
     BlockPlan plan;
     bool keep;             // a block launch that also stores the state of the step before its last
     // check records [lo, hi) it writes (or reads: reductions), and the first-stage records of a reduction
     const DD *lo, *hi, *glo, *ghi;
 };
 static std::vector<Launch> launches;
-static std::function<float(const Launch&)> cost_us;   // what the autotuner's events report
-static double clock_us = 0.0;
+static std::function<double(const Launch&)> cost_us;  // what the autotuner's events report
 
 static void note(Launch l) {
-    if (cost_us) clock_us += cost_us(l);
+    if (cost_us) stub::clock_us += cost_us(l);
     launches.push_back(l);
 }
 static void records(Launch* l, const StepArgs& a, bool check) {
@@ -38,13 +37,13 @@ hipError_t launch_step(int, const Shape&, int mode, const StepArgs& a, int64_t, 
     return hipSuccess;
 }
 hipError_t launch_fused(int, const Shape&, const StepArgs& a, int k, int end, int, int, int64_t, hipStream_t st) {
-    Launch l{st, 1, k, end, a.march_rows};
+    Launch l{st, 1, k, end, a.march_rows, a.ntiles};
     records(&l, a, end == kEndCheck);
     note(l);
     return hipSuccess;
 }
 hipError_t launch_block(int, const BlockPlan& p, const Shape&, const BlockArgs& b, int end, hipStream_t st) {
-    Launch l{st, 2, b.steps, end, 0, p, b.prev != nullptr};
+    Launch l{st, 2, b.steps, end, 0, b.s.ntiles, p, b.prev != nullptr};
     records(&l, b.s, end == kEndCheck);
     note(l);
     return hipSuccess;
@@ -82,9 +81,6 @@ hipError_t launch_fill(void*, size_t, uint32_t, hipStream_t) { return hipSuccess
 hipError_t preload_fused(int, int, int, int, hipStream_t) { return hipSuccess; }
 }
 
-static std::map<hipEvent_t, double> event_us;
-extern "C" hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
-
 // ------------------------------------------------------------------ handles
 
 static lbm_instance inst(int nx, int ny) {
@@ -100,7 +96,13 @@ static lbm_instance inst(int nx, int ny) {
     return in;
 }
 
-static lbm_handle make(const std::vector<lbm_instance>& v, int storage, int check, int flags = 0) {
+static void start(lbm_handle h, size_t n) {
+    static const double field = 1.0;
+    for (size_t k = 0; h && k < n; ++k)
+        expect(lbm_init_device(h, (int32_t)k, &field, nullptr, nullptr) == LBM_OK, "init");
+}
+
+static lbm_handle make(const std::vector<lbm_instance>& v, int storage, int check, int flags = 0, bool init = true) {
     lbm_config c;
     std::memset(&c, 0, sizeof c);
     c.n_instances = (int32_t)v.size();
@@ -110,8 +112,7 @@ static lbm_handle make(const std::vector<lbm_instance>& v, int storage, int chec
     c.inst = v.data();
     lbm_handle h = nullptr;
     expect(lbm_create(&c, &h) == LBM_OK, "create");
-    static const double field = 1.0;
-    for (size_t k = 0; h && k < v.size(); ++k) expect(lbm_init_device(h, (int32_t)k, &field, nullptr, nullptr) == LBM_OK, "init");
+    if (init) start(h, v.size());
     return h;
 }
 
@@ -153,9 +154,49 @@ static void streams() {
             }
 }
 
+// Strips of fused launches: by the launch's steps, whatever set the steps per
+// launch (a new handle's default with short calls, a setting, the autotuner).
+static void strips() {
+    struct Size {
+        int nx, ny, few, many;   // rows per strip below kTallSteps steps, and from there on
+    };
+    for (const Size& s : {Size{8192, 8192, 32, 64}, Size{8192, 8222, 32, 64}, Size{2600, 2300, 32, 32},
+                          Size{1500, 1400, 16, 16}})
+        for (int storage : {LBM_F16, LBM_BF16_SPLIT})
+            for (int how = 0; how < 3; ++how)
+                for (int k = 2; k <= fuse_max(storage); ++k) {
+                    lbm_handle h = make({inst(s.nx, s.ny)}, storage, how == 0 ? 4 : -1, 0, false);
+                    if (how == 1) expect(lbm_set_step_fusion(h, k) == LBM_OK, "step fusion");
+                    if (how == 2) {
+                        cost_us = [k](const Launch& l) { return l.kind == 1 && l.steps == k ? 1.0 * k : 10.0 * l.steps; };
+                        expect(lbm_autotune(h, 4, nullptr, 0) == LBM_OK, "autotune");
+                        cost_us = nullptr;
+                        expect(lbm_get_step_fusion(h) == k, "tuned steps per launch");
+                    }
+                    start(h, 1);
+                    launches.clear();
+                    for (int call : {k, 4 * k, 3}) expect(lbm_step(h, call) == LBM_OK, "step");
+                    double dT = 0.0;
+                    expect(lbm_moments_f64(h, 0, &dT, nullptr, nullptr, 1) == LBM_OK, "moments");
+                    const int tx = (int)fused_tiles_x(h->inst[0], storage);
+                    int seen = 0;
+                    for (const Launch& l : launches) {
+                        if (l.kind != 1) continue;
+                        ++seen;
+                        const int rows = l.end != kEndCheck && l.steps < kTallSteps ? s.few : s.many;
+                        expect(l.rows == rows, "rows of a strip");
+                        const int chunks = (s.ny + s.many - 1) / s.many;
+                        expect(l.tiles == tx * chunks * (rows < s.many ? 2 : 1), "strips of a launch");
+                    }
+                    expect(seen >= 2, "fused launches");
+                    lbm_destroy(h);
+                }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "streams") streams();
+    else if (what == "strips") strips();
     else expect(false, "unknown check");
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -36,3 +36,9 @@ def test_streams_share_no_check_records(driver):
     """Two streams of one call, a lone check step before block or fused check
     launches among the calls: neither writes records the other uses."""
     driver("lattice_launches", "streams")
+
+
+def test_strips_follow_the_steps_of_a_launch(driver):
+    """Few-step launches of large 16-bit handles take strips of half the
+    height, in short calls, after lbm_set_step_fusion and after lbm_autotune."""
+    driver("lattice_launches", "strips")
