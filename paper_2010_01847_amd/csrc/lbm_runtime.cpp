@@ -312,13 +312,35 @@ double block_cost(const std::vector<lbm_instance>& v, const BlockPlan& p, int st
     return (3.4 + p.halo * step * std::max(1.0, rounds) + traffic * (rounds > 1.0 ? 0.6 : 1.0)) / p.halo;
 }
 
+// Expected time of one step in single-step launches, in microseconds: launch
+// latency, or the nodes' traffic, or the lanes of 64-node chunks that short rows
+// leave idle.  Measured (FP32): 128 x 64 3.0, 700 x 571 5.6, 1024^2 11.2, 2048^2
+// 38.7; 8000 lattices of 20 x 20 23.5; 200000 x 3 6.1; 3 x 200000 32.2.
+double single_cost(const std::vector<lbm_instance>& v) {
+    double nodes = 0.0, lanes = 0.0;                            // in millions
+    for (auto& in : v) {
+        nodes += 1e-6 * in.nx * in.ny;
+        lanes += 1e-6 * ((in.nx + 63) / 64 * 64.0) * in.ny;
+    }
+    return std::max({3.4, 1.6 + 9.0 * nodes, 1.6 + 2.5 * lanes});
+}
+
 // The block kernels' plan for a handle's lattices (kBlockNone: too large for
-// them).  Up to kBlockModelNodes the cheapest by block_cost; above, where many
-// rounds of blocks overlap each other's loads, steps and stores, one tile that
-// is within 2% of the best of 40 tried there (FP32 us per step, this tile /
-// best tile / marching kernel at seven steps: 999 x 777 3.79 / 3.79 / 12.0,
-// 1500 x 1100 6.95 / 6.95 / 13.3, 2048^2 15.7 / 15.7 / 17.8, 2400^2 22.6 /
-// 22.2 / 22.1: kBlockNodes lies between the last two).
+// them, or of a shape that wastes their windows).  Up to kBlockModelNodes the
+// cheapest by block_cost; above, where many rounds of blocks overlap each
+// other's loads, steps and stores, one tile that is within 2% of the best of 40
+// tried on lattices of both sides well above its window (FP32 us per step, this
+// tile / best tile / marching kernel at seven steps: 999 x 777 3.79 / 3.79 /
+// 12.0, 1500 x 1100 6.95 / 6.95 / 13.3, 2048^2 15.7 / 15.7 / 17.8, 2400^2 22.6 /
+// 22.2 / 22.1: kBlockNodes lies between the last two), or whole lattices where
+// that is cheaper.  Either way only where it is expected 3% below single steps:
+// windows hold up to 30 nodes per node of a thin lattice.  Measured (FP32 us per
+// step over 100 steps, the tile / whole lattices / without block kernels; *: the
+// choice): 200000 x 3 12.9 / - / 6.1*, 100000 x 8 7.6 / - / 6.2*, 1000000 x 2
+// 56.9 / - / 22.5*, 20000 x 40 6.5* / - / 9.4, 16 x 60000 10.3* / - / 13.2,
+// 100000 x 3 (its best window) 4.8 / - / 4.3*, 3 x 200000 31.1 / - / 32.2*; 2000 of 20 x 20 8.7 / 1.9* / 10.2,
+// 8000 of 20 x 20 34.2 / 6.4* / 23.5, 4000 of 32 x 32 20.8 / 7.1* / 18.9, 1500 of
+// 401 x 3 39.9 / 4.4* / 14.3.
 BlockPlan block_plan(const std::vector<lbm_instance>& v, int storage) {
     int64_t most = 0, nodes = 0;
     for (auto& in : v) {
@@ -327,14 +349,7 @@ BlockPlan block_plan(const std::vector<lbm_instance>& v, int storage) {
     }
     BlockPlan best;
     if (nodes > kBlockNodes) return best;
-    if (nodes > kBlockModelNodes) {
-        best.kind = kBlockTiles;
-        best.rows = 4;
-        best.waves = 12;
-        best.halo = 7;
-        return best;
-    }
-    double cost = 1e300;
+    double cost = 0.97 * single_cost(v);      // (3 x 200000: even in FP32, 3% slower rounding every step to FP16)
     auto consider = [&](const BlockPlan& p) {
         const double c = block_cost(v, p, storage);
         if (c < cost) {
@@ -348,6 +363,15 @@ BlockPlan block_plan(const std::vector<lbm_instance>& v, int storage) {
         p.rows = most <= 1024 ? 1 : 2;
         p.waves = (int)((most + 64 * p.rows - 1) / (64 * p.rows));
         consider(p);
+    }
+    if (nodes > kBlockModelNodes) {
+        BlockPlan p;
+        p.kind = kBlockTiles;
+        p.rows = 4;
+        p.waves = 12;
+        p.halo = 7;
+        consider(p);
+        return best;
     }
     static const int windows[4][2] = {{32, 32}, {28, 28}, {32, 24}, {24, 24}};
     for (auto& w : windows)

@@ -193,10 +193,39 @@ static void strips() {
                 }
 }
 
+// Plans of the block kernels by the shapes of a handle's lattices.
+static void plans() {
+    struct Case {
+        int count, nx, ny;
+        BlockKind kind;
+    };
+    const Case cases[] = {
+        // one lattice of each size class
+        {1, 2, 2, kBlockWhole}, {1, 401, 3, kBlockWhole}, {1, 128, 64, kBlockPatch}, {1, 201, 201, kBlockPatch},
+        {1, 999, 777, kBlockTiles}, {1, 1024, 256, kBlockTiles}, {1, 2000, 2000, kBlockTiles}, {1, 4000, 4000, kBlockNone},
+        // thin lattices: windows mostly outside of them
+        {1, 200000, 3, kBlockNone}, {1, 100000, 8, kBlockNone}, {1, 1000000, 2, kBlockNone}, {1, 500000, 5, kBlockNone},
+        {1, 2, 1000000, kBlockNone}, {1, 3, 200000, kBlockNone}, {1, 100000, 3, kBlockNone}, {1, 100000, 2, kBlockNone},
+        {1, 20000, 40, kBlockTiles}, {1, 40, 20000, kBlockTiles}, {1, 16, 60000, kBlockTiles}, {1, 8000, 100, kBlockTiles},
+        // many small ones
+        {2000, 20, 20, kBlockWhole}, {8000, 20, 20, kBlockWhole}, {4000, 32, 32, kBlockWhole}, {1000, 41, 25, kBlockWhole},
+        {400, 401, 3, kBlockWhole}, {1500, 401, 3, kBlockWhole}, {500, 64, 32, kBlockWhole}, {300, 100, 40, kBlockTiles},
+        {20000, 20, 20, kBlockNone},
+    };
+    for (const Case& c : cases) {
+        const BlockPlan p = block_plan(std::vector<lbm_instance>((size_t)c.count, inst(c.nx, c.ny)), LBM_F32);
+        if (p.kind != c.kind) {
+            std::printf("%d of %d x %d: plan %d, expected %d\n", c.count, c.nx, c.ny, p.kind, c.kind);
+            expect(false, "plan");
+        }
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "streams") streams();
     else if (what == "strips") strips();
+    else if (what == "plans") plans();
     else expect(false, "unknown check");
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -42,3 +42,9 @@ def test_strips_follow_the_steps_of_a_launch(driver):
     """Few-step launches of large 16-bit handles take strips of half the
     height, in short calls, after lbm_set_step_fusion and after lbm_autotune."""
     driver("lattice_launches", "strips")
+
+
+def test_block_plans_by_shape(driver):
+    """The block kernels take a handle's lattices where their windows fit them:
+    not thin ones, and whole lattices where a handle holds many small ones."""
+    driver("lattice_launches", "plans")
