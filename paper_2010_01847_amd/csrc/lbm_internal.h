@@ -225,7 +225,7 @@ struct BlockPlan {
 
 // Most nodes of a handle (all instances) that runs in the block kernels, and
 // up to which their plan comes from the cost model (see block_plan).
-constexpr int64_t kBlockNodes = 4500000;
+constexpr int64_t kBlockNodes = 4300000;
 constexpr int64_t kBlockModelNodes = 400000;
 // Most steps of one launch of a whole lattice.
 constexpr int kWholeSteps = 512;

@@ -522,7 +522,7 @@ struct lbm_ctx {
     int64_t npgroups = 0;
     int march_rows = kMarchRows;       // fused kernel: output rows per strip
     BlockPlan bplan;                   // block kernels (kBlockNone: not for these instances)
-    bool block_on = false;             // single steps run in the block kernels (see plan_block)
+    bool block_on = false;             // single steps run in the block kernels (see plan_next)
     std::vector<int32_t> btile_inst;   // block kernels: tile -> instance
     std::vector<int32_t> bgroup_inst;  // block kernels: reduction group -> instance
     // The instances one launch covers: all of them, or one of the parts that
@@ -563,8 +563,9 @@ struct lbm_ctx {
         int src = 0;           // buffer that launch read
         int apply_shift = 0;   // its first step applied the pending reference shift
         int checked = 0;       // it ended on a check step (the reference moved after it)
-        int kept = 0;          // a block-kernel launch that also stored the state of step n - 1
-                               // in the readout buffer: nothing to replay
+        int block = 0;         // it was a block-kernel launch
+        int kept = 0;          // which also stored the state of step n - 1 in the readout
+                               // buffer: nothing to replay
     } tail, graph_tail;
     int graph_tail_flip = 0;           // launches of a captured chunk before its last one, mod 2
     bool replayed = false;             // the readout buffer holds the replayed state
@@ -1400,15 +1401,61 @@ static int issue_fused(lbm_ctx* h, int64_t m, int nsteps, int end, int src_k, hi
     return LBM_OK;
 }
 
-// Steps the block-kernel launch that starts at step m covers, in a sequence
-// of steps that ends at step `last`; 1: a single-step launch.  The steps up to
-// the next check step (or `last`) are shared out evenly over the fewest
-// launches, so that the one that reaches the check step has at least two (it
-// forms the residual against the step before).  A call's last step runs single
-// where it is the snapshot step before a check step, and so does the lone
-// check step that then starts the next call.
-static int plan_block(const lbm_ctx* h, int64_t m, int64_t last, int* end) {
-    *end = kEndPlain;
+// A launch of a sequence of steps.
+enum LaunchKind { kSingle = 0, kFused = 1, kBlock = 2 };
+struct Next {
+    LaunchKind kind;
+    int k;      // steps
+    int end;    // FusedEnd
+};
+
+// The launch of a handle without block kernels.
+static Next next_march(const lbm_ctx* h, int64_t m, int64_t last) {
+    Next n;
+    n.k = plan_launch(h, m, last, &n.end);
+    n.kind = n.k >= 2 ? kFused : kSingle;
+    return n;
+}
+
+// Up to how many steps a handle in the block kernels leaves to the launches it
+// would have without them.  A block launch loads whole windows and stores the
+// lattice however few its steps are, and one that ends a call also stores the
+// state before (keep_prev) or has it replayed by a readout.  Where the marching
+// kernel is there (handles of kFuseMinStrips strips or more), it or a single
+// step takes few steps faster; FP32 us per call, march / block: two steps 1500 x
+// 1400 35.9 / 36.1, 1700 x 1500 35.5 / 43.0, 2048^2 49 / 111; four steps 1500 x
+// 1400 53 / 42, 1700 x 1500 53 / 49, 2048^2 66 / 112, even without the state
+// before 67; FP32 stochastic and 16-bit rounding every step reach that point
+// later: FP32-SR four steps 2048^2 160 / 138, FP16-SR two 1700 x 1500 40.6 /
+// 35.6, 2048^2 49.6 / 54.8, three 67.5 / 69.7.  Without it, two steps run as
+// single ones: 512^2 8.9 / 9.6, 401 x 301 7.1 / 7.3, 2 x 100000 44 / 62, but 128
+// x 64 6.0 / 4.8 and whole lattices always faster (1000 of 41 x 25 60 / 41).
+static int few_steps(const lbm_ctx* h) {
+    if (h->bplan.kind == kBlockWhole) return 1;
+    if (h->fuse < 2) return h->L.nodes >= 100000 ? 2 : 1;
+    if (h->storage != LBM_F32) return h->L.buf_bytes > (size_t)58 << 20 ? 3 : 1;
+    if (h->sr) return 1;
+    return h->L.buf_bytes > (size_t)73 << 20 ? 4 : 2;
+}
+
+// The launch that starts at step m in a sequence of steps that ends at step
+// `last`.  Handles in the block kernels: the steps up to the next check step
+// (or `last`) are shared out evenly over the fewest launches, so that the one
+// that reaches the check step has at least two (it forms the residual against
+// the step before).  A call's last step runs single where it is the snapshot
+// step before a check step, and so does the lone check step that then starts
+// the next call.  Few steps (few_steps) are left to the other launches, and
+// where the marching kernel is there, so are the last h->fuse steps up to a
+// check step: a block launch that ends on one takes 29 us (1024^2) to 110 us
+// (2000^2) more than a plain one, the marching kernel's 10 to 40% (FP32, five
+// steps up to a check step, us, march / block: 1500 x 1400 92 / 109, 1700 x 1500
+// 92 / 129, 2000^2 115 / 213; FP16-SR 116 / 117, 118 / 137, 142 / 215).  FP32
+// stochastic below 73 MB is faster in the block kernels from four steps on
+// (1500 x 1400, three steps 117 / 119, five 192 / 166), and without the marching
+// kernel up to a check step from eight (1024 x 1000, single steps / block, five
+// steps 94 / 99, seven 120 / 128, ten 158 / 154; 640^2 always in blocks).
+static Next plan_next(const lbm_ctx* h, int64_t m, int64_t last) {
+    if (!h->block_on) return next_march(h, m, last);
     int64_t seg = last;
     bool to_check = false;
     if (h->K) {
@@ -1420,12 +1467,41 @@ static int plan_block(const lbm_ctx* h, int64_t m, int64_t last, int* end) {
     }
     int64_t r = seg - m + 1;
     if (!to_check && mode_of(h, seg) == kSnap) --r;
-    if (r < 2) return 1;
+    const bool march = h->fuse >= 2;
+    const bool sr32 = h->sr && h->storage == LBM_F32;
+    const bool small_sr = sr32 && h->L.buf_bytes <= (size_t)73 << 20;
+    int few = few_steps(h), rest = 0;
+    if (to_check) {
+        if (march && !small_sr) rest = h->fuse;
+        else few = march ? 3 : (sr32 && h->L.nodes > 700000 ? 7 : 1);
+    }
+    if (r <= few + rest) return march ? next_march(h, m, last) : Next{kSingle, 1, kEndPlain};
+    r -= rest;
+    if (r < 2) return {kSingle, 1, kEndPlain};
     const int64_t most = h->bplan.kind == kBlockWhole ? kWholeSteps : h->bplan.halo;
     const int64_t n = (r + most - 1) / most;
     const int k = (int)((r + n - 1) / n);
-    if (k == r && to_check) *end = kEndCheck;
-    return k;
+    return {kBlock, k, k == r && to_check && !rest ? kEndCheck : kEndPlain};
+}
+
+// Whether a block launch of k steps that ends a call (or a captured chunk) also
+// stores the state of the step before its last, which readouts start from: where
+// the three buffers stay in the 256 MB last-level cache the store costs less
+// than the replay of k - 1 steps by the first readout (FP32, calls of seven steps
+// without readout, us, not stored / stored: 512^2 14.6 / 15.7, 1024^2 35.7 / 36.9,
+// 1700 x 1500 64 / 67, but 2048^2 101 / 117 and of two steps 52 / 111), and so it
+// does after many steps (whole lattices).
+static bool keep_prev(const lbm_ctx* h, int k) { return 3 * h->L.buf_bytes <= (size_t)256 << 20 || k > 16; }
+
+// The plan's part of a block launch's arguments, for k steps.
+static void block_args(const lbm_ctx* h, int k, BlockArgs* b) {
+    b->s.tile_inst = h->d_btiles();
+    b->prev = nullptr;
+    b->steps = k;
+    b->halo = h->bplan.halo;
+    b->waves = h->bplan.waves;
+    b->win_x = h->bplan.win_x();
+    b->win_y = h->bplan.win_y();
 }
 
 // Issue k steps from step m in the block kernels; keep: also store the state
@@ -1433,9 +1509,9 @@ static int plan_block(const lbm_ctx* h, int64_t m, int64_t last, int* end) {
 static int issue_block(lbm_ctx* h, int64_t m, int k, int end, int src_k, bool keep, hipStream_t st,
                        const lbm_ctx::Span& sp) {
     BlockArgs b;
+    block_args(h, k, &b);
     StepArgs& a = b.s;
     a.desc = h->d_desc();
-    a.tile_inst = h->d_btiles();
     a.src = h->buf(src_k);
     a.dst = h->buf(1 - src_k);
     a.snap = nullptr;
@@ -1448,12 +1524,7 @@ static int issue_block(lbm_ctx* h, int64_t m, int k, int end, int src_k, bool ke
     a.apply_shift = (h->K > 0 && (m - 1) % h->K == 0) ? 1 : 0;
     a.tile_base = sp.bt0;
     a.ntiles = sp.bnt;
-    b.prev = keep ? h->buf(lbm_ctx::kReadout) : nullptr;
-    b.steps = k;
-    b.halo = h->bplan.halo;
-    b.waves = h->bplan.waves;
-    b.win_x = h->bplan.win_x();
-    b.win_y = h->bplan.win_y();
+    if (keep) b.prev = h->buf(lbm_ctx::kReadout);
     HIPCALL(h, launch_block(h->storage, h->bplan, h->shape, b, end, st));
     if (end == kEndCheck)
         HIPCALL(h, launch_finalize(h->d_desc(), h->d_bgroups(), sp.bg0, sp.bng, h->d_ref(), h->d_ref_prev(), sp.i0,
@@ -1504,23 +1575,24 @@ static int capture(lbm_ctx* h, int par) {
     lbm_ctx::Tail tail;
     int tail_flip = 0;
     for (int s = 1; s <= C && rc == LBM_OK;) {
-        int end = kEndPlain;
-        const bool block = h->block_on;
-        const int k = block ? plan_block(h, s, C, &end) : plan_launch(h, s, C, &end);
-        const bool keep = block && s + k - 1 == C;
+        const Next next = plan_next(h, s, C);
+        const int k = next.k;
+        const bool block = next.kind == kBlock;
+        const bool keep = block && s + k - 1 == C && keep_prev(h, k);
         tail = lbm_ctx::Tail();
         tail_flip = flips & 1;
         for (int p = 0; p < np && rc == LBM_OK; ++p) {
             hipStream_t st = p == 0 ? h->capture_stream : h->cap_part_stream;
             const lbm_ctx::Span& sp = multi ? h->part[p] : h->all;
-            rc = k >= 2 ? (block ? issue_block(h, (int64_t)s, k, end, src, keep, st, sp)
-                                 : issue_fused(h, (int64_t)s, k, end, src, st, sp))
+            rc = k >= 2 ? (block ? issue_block(h, (int64_t)s, k, next.end, src, keep, st, sp)
+                                 : issue_fused(h, (int64_t)s, k, next.end, src, st, sp))
                         : issue_step(h, (int64_t)s, src, st, LBM_SCHED_BATCHED, sp);
         }
         if (k >= 2) {
             tail.k = k;
             tail.apply_shift = (h->K > 0 && (s - 1) % h->K == 0) ? 1 : 0;
-            tail.checked = end == kEndCheck ? 1 : 0;
+            tail.checked = next.end == kEndCheck ? 1 : 0;
+            tail.block = block ? 1 : 0;
             tail.kept = keep ? 1 : 0;
         }
         s += k;
@@ -1577,24 +1649,25 @@ static int step_loop(lbm_ctx* h, int64_t nsteps, bool multi) {
         // the per-instance schedule issues single steps: one instance's fused
         // launch holds too few wavefronts to hide the marching latency
         // (Knudsen sweep: 4.0k MLUPS at five steps per launch, 17.1k single)
-        int end = kEndPlain;
-        const bool block = h->block_on && sched != LBM_SCHED_PER_INSTANCE;
-        const int k = sched == LBM_SCHED_PER_INSTANCE ? 1
-                      : block ? plan_block(h, m, h->steps + left, &end) : plan_launch(h, m, h->steps + left, &end);
-        const bool keep = block && k == left;
+        const Next next =
+            sched == LBM_SCHED_PER_INSTANCE ? Next{kSingle, 1, kEndPlain} : plan_next(h, m, h->steps + left);
+        const int k = next.k;
+        const bool block = next.kind == kBlock;
+        const bool keep = block && k == left && keep_prev(h, k);
         h->tail = lbm_ctx::Tail();
         if (k >= 2) {
             for (int p = 0; p < np; ++p) {
-                int rc = block ? issue_block(h, m, k, end, h->cur, keep, stream_of(p), span_of_part(p))
-                               : issue_fused(h, m, k, end, h->cur, stream_of(p), span_of_part(p));
+                int rc = block ? issue_block(h, m, k, next.end, h->cur, keep, stream_of(p), span_of_part(p))
+                               : issue_fused(h, m, k, next.end, h->cur, stream_of(p), span_of_part(p));
                 if (rc) return rc;
             }
+            h->tail.block = block ? 1 : 0;
             h->tail.kept = keep ? 1 : 0;
             h->tail.k = k;
             h->tail.src = h->cur;
             h->tail.apply_shift = (h->K > 0 && (m - 1) % h->K == 0) ? 1 : 0;
-            h->tail.checked = end == kEndCheck ? 1 : 0;
-            if (end == kEndCheck) h->last_check = m + k - 1;
+            h->tail.checked = next.end == kEndCheck ? 1 : 0;
+            if (next.end == kEndCheck) h->last_check = m + k - 1;
             h->cur = 1 - h->cur;
             h->steps = m + k - 1;
             left -= k;
@@ -1623,7 +1696,7 @@ int lbm_step(lbm_handle h, int64_t nsteps) {
         h->replayed = false;
         h->desc_saved = false;
     }
-    if (nsteps > 0 && !h->preloaded && !h->block_on) {
+    if (nsteps > 0 && !h->preloaded && (!h->block_on || h->fuse >= 2)) {
         HIPCALL(h, preload_fused(h->storage, h->sr, h->layout == LBM_LAYOUT_CHUNKED, h->every_step, h->stream));
         h->preloaded = true;
     }
@@ -1652,9 +1725,12 @@ int lbm_step(lbm_handle h, int64_t nsteps) {
 // of its step-n nodes go to the readout buffer (as planes laid out like the
 // snapshot), from the same registers the launch itself relaxed.
 // That launch also writes the moments of instance k to the arrays of `out`.
+// Block launches round every step of either kind of storage and are replayed
+// in the block kernels.
 static int replay_tail(lbm_ctx* h, int32_t k = -1, double* const* out = nullptr) {
     const lbm_ctx::Tail& t = h->tail;
-    StepArgs a;
+    BlockArgs b;
+    StepArgs& a = b.s;
     if (out) {
         a.out_inst = k;
         for (int c = 0; c < 3; ++c) a.out[c] = out[c];
@@ -1672,7 +1748,11 @@ static int replay_tail(lbm_ctx* h, int32_t k = -1, double* const* out = nullptr)
     a.ref = t.checked ? h->d_ref_prev() : h->d_ref();
     a.apply_shift = t.apply_shift;
     a.tile_base = 0;
-    if (!h->every_step) {
+    if (t.block) {
+        block_args(h, t.k - 1, &b);
+        a.ntiles = (int32_t)h->btile_inst.size();
+        HIPCALL(h, launch_block(h->storage, h->bplan, h->shape, b, kEndPlain, h->stream));
+    } else if (!h->every_step) {
         a.snap = reinterpret_cast<double*>(h->buf(lbm_ctx::kReadout));
         a.tile_inst = h->d_ptiles();
         strips_for(h, t.k, kEndMoments, 0, (int32_t)h->ptile_inst.size(), &a);
@@ -1705,11 +1785,11 @@ static int run_moments(lbm_ctx* h, int32_t k, int out_kind, void* T, void* qx, v
         if (!h->replayed && !h->tail.kept) {
             // a 16-bit replay forms the moments themselves: FP64 arrays are
             // written by it, without a pass over the readout buffer
-            const bool direct = !h->every_step && out_kind == 1 && !partials;
+            const bool direct = !h->every_step && !h->tail.block && out_kind == 1 && !partials;
             int rc = replay_tail(h, k, direct ? out : nullptr);
             if (rc || direct) return rc;
         }
-        if (!h->every_step && !h->tail.kept) {
+        if (!h->every_step && !h->tail.block) {
             HIPCALL(h, launch_plane_moments(h->d_desc_last(), k, h->desc[k],
                                             reinterpret_cast<const double*>(h->buf(lbm_ctx::kReadout)), h->L.nodes,
                                             out_kind, T, qx, qy, in.t0, grad, partials, h->stream));
@@ -2079,9 +2159,9 @@ static int time_block(lbm_ctx* h, int steps, hipEvent_t e0, hipEvent_t e1, float
     const int k = h->bplan.kind == kBlockWhole ? 32 : h->bplan.halo;
     const int launches = (steps + k - 1) / k;
     BlockArgs b;
+    block_args(h, k, &b);
     StepArgs& a = b.s;
     a.desc = h->d_desc();
-    a.tile_inst = h->d_btiles();
     a.snap = nullptr;
     a.partials = nullptr;
     a.tile_base = 0;
@@ -2090,12 +2170,6 @@ static int time_block(lbm_ctx* h, int steps, hipEvent_t e0, hipEvent_t e1, float
     a.sr = h->sr;
     a.ref = h->d_ref();
     a.apply_shift = 0;
-    b.prev = nullptr;
-    b.steps = k;
-    b.halo = h->bplan.halo;
-    b.waves = h->bplan.waves;
-    b.win_x = h->bplan.win_x();
-    b.win_y = h->bplan.win_y();
     int src = 0;
     for (int w = 0; w < 2 + launches; ++w) {
         if (w == 2) HIPCALL(h, hipEventRecord(e0, h->stream));
@@ -2211,16 +2285,18 @@ int lbm_autotune(lbm_handle h, int32_t steps, char* report, size_t report_len) {
             }
         }
     }
-    // the block kernels, which replace single steps (the same bits); for FP32
-    // storage and 16-bit storage rounding every step they replace fused
-    // launches too
+    // the block kernels, which replace single steps (the same bits), and for FP32
+    // storage and 16-bit storage rounding every step also fused launches, which
+    // then stay for few steps (plan_next).  Other 16-bit storage keeps fused
+    // launches where they beat single steps even if the block kernels beat both:
+    // they round less often.
     float block_us = 1e30f;
     if (!rc && h->bplan.kind != kBlockNone) rc = time_block(h, steps, e0, e1, &block_us);
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    const int fuse = fused_us < best_us && (!h->every_step || fused_us < block_us) ? fused_k : 1;
-    const bool block = fuse == 1 && block_us < best_us;
+    const int fuse = fused_us < best_us ? fused_k : 1;
+    const bool block = block_us < best_us && (fuse == 1 || (h->every_step && block_us < fused_us));
     // the planner's launch costs: the measured plain launches, the check
     // launches scaled from the built-in figures by the same ratio
     {

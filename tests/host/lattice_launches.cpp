@@ -221,11 +221,80 @@ static void plans() {
     }
 }
 
+// Few steps, check steps and the state before a call's last step on handles in
+// the block kernels.
+static void short_runs() {
+    auto kinds = [](lbm_handle h, int n) {       // kinds of a call's launches; 4: one more by a readout
+        launches.clear();
+        expect(lbm_step(h, n) == LBM_OK, "step");
+        std::string s;
+        for (const Launch& l : launches)
+            if (l.kind != 3) s += std::to_string(l.kind);
+        launches.clear();
+        double dT = 0.0;
+        expect(lbm_moments_f64(h, 0, &dT, nullptr, nullptr, 1) == LBM_OK, "moments");
+        return s + (launches.empty() ? "" : "+" + std::to_string(launches[0].kind));
+    };
+    auto same = [](const std::string& got, const char* want, const char* what) {
+        if (got != want) std::printf("%s: launched %s, expected %s\n", what, got.c_str(), want);
+        expect(got == want, what);
+    };
+    struct Case {
+        int nx, ny, storage, flags;
+        const char *two, *three, *four, *seven;  // kinds launched by calls of that many steps
+    };
+    const int every = LBM_FLAG_ROUND_EVERY_STEP, sr = LBM_FLAG_STOCHASTIC_ROUNDING;
+    for (const Case& c : {Case{128, 64, LBM_F32, 0, "2", "2", "2", "2"}, Case{512, 512, LBM_F32, 0, "00", "2", "2", "2"},
+                          Case{1000, 1000, LBM_F16, 0, "00", "2", "2", "2"},
+                          Case{1500, 1400, LBM_F32, 0, "1+0", "2", "2", "2"},
+                          Case{1700, 1500, LBM_F32, 0, "1+0", "1+1", "1+1", "2"},
+                          Case{2048, 2048, LBM_F32, 0, "1+0", "1+1", "1+1", "2+2"},
+                          Case{2048, 2048, LBM_F32, sr, "2+2", "2+2", "2+2", "2+2"},
+                          Case{2048, 2048, LBM_F16, every, "1+0", "1+1", "2", "2"},
+                          Case{1500, 1400, LBM_F16, every, "2", "2", "2", "2"}}) {
+        lbm_handle h = make({inst(c.nx, c.ny)}, c.storage, -1, c.flags);
+        same(kinds(h, 2), c.two, "two steps");
+        same(kinds(h, 3), c.three, "three steps");
+        same(kinds(h, 4), c.four, "four steps");
+        same(kinds(h, 7), c.seven, "seven steps");
+        lbm_destroy(h);
+    }
+    // a segment's last launches up to a check step
+    for (int n : {2000, 1500, 1000, 700})
+        for (int flags : {0, sr})
+            for (int check : {2, 3, 5, 10, 20, 100}) {
+                lbm_handle h = make({inst(n, n)}, LBM_F32, check, flags);
+                launches.clear();
+                expect(lbm_step(h, 2 * check) == LBM_OK, "step");
+                for (const Launch& l : launches)
+                    if (l.kind < 3 && l.end == kEndCheck)
+                        expect(l.kind == (n == 1000 && flags ? 0 : n <= 1000 || (n == 1500 && flags && check > 3) ? 2 : 1),
+                               "check launch");
+                lbm_destroy(h);
+            }
+    // many small lattices: long launches keep the state before the last step,
+    // short ones of buffers beyond the last-level cache do not
+    lbm_handle h = make(std::vector<lbm_instance>(2500, inst(20, 20)), LBM_F32, -1);
+    same(kinds(h, 100), "22", "100 steps of many lattices");
+    same(kinds(h, 7), "22+2", "seven steps of many lattices");
+    lbm_destroy(h);
+    // tuned to the block kernels, a handle keeps fused launches for few steps
+    h = make({inst(2048, 2048)}, LBM_F32, -1, 0, false);
+    cost_us = [](const Launch& l) { return l.kind == 2 ? 1.0 : l.kind == 1 ? 10.0 : 5.0 * l.steps; };
+    expect(lbm_autotune(h, 4, nullptr, 0) == LBM_OK, "autotune");
+    cost_us = nullptr;
+    start(h, 1);
+    same(kinds(h, 7), "2+2", "seven steps, tuned");
+    same(kinds(h, 3), "1+1", "three steps, tuned");
+    lbm_destroy(h);
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "streams") streams();
     else if (what == "strips") strips();
     else if (what == "plans") plans();
+    else if (what == "short_runs") short_runs();
     else expect(false, "unknown check");
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -48,3 +48,9 @@ def test_block_plans_by_shape(driver):
     """The block kernels take a handle's lattices where their windows fit them:
     not thin ones, and whole lattices where a handle holds many small ones."""
     driver("lattice_launches", "plans")
+
+
+def test_few_steps_and_check_steps_of_block_handles(driver):
+    """Which kernels take few steps, check steps and a readout's replay of
+    handles in the block kernels."""
+    driver("lattice_launches", "short_runs")
