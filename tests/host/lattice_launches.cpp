@@ -289,12 +289,31 @@ static void short_runs() {
     lbm_destroy(h);
 }
 
+// Pinned memory of a new handle: none unless it has many check records to copy;
+// none by lbm_last_check itself.
+static void pinned() {
+    struct Case {
+        int count, check, allocs;
+    };
+    for (const Case& c : {Case{1, 100, 0}, Case{1, -1, 0}, Case{7, 10, 0}, Case{8, 10, 1}, Case{256, -1, 0}, Case{256, 100, 1}}) {
+        const int before = stub::host_allocs;
+        lbm_handle h = make(std::vector<lbm_instance>((size_t)c.count, inst(40, 30)), LBM_F32, c.check);
+        expect(stub::host_allocs - before == c.allocs, "pinned allocations at creation");
+        lbm_check_info info;
+        expect(lbm_step(h, 100) == LBM_OK, "step");
+        expect(lbm_last_check(h, 0, &info) == (c.check > 0 ? LBM_OK : LBM_ESTATE), "last check");
+        expect(stub::host_allocs - before == c.allocs, "pinned allocations by lbm_last_check");
+        lbm_destroy(h);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "streams") streams();
     else if (what == "strips") strips();
     else if (what == "plans") plans();
     else if (what == "short_runs") short_runs();
+    else if (what == "pinned") pinned();
     else expect(false, "unknown check");
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -54,3 +54,9 @@ def test_few_steps_and_check_steps_of_block_handles(driver):
     """Which kernels take few steps, check steps and a readout's replay of
     handles in the block kernels."""
     driver("lattice_launches", "short_runs")
+
+
+def test_new_handles_pin_no_memory_without_use(driver):
+    """lbm_create pins host memory only for handles with many check records;
+    lbm_last_check never allocates."""
+    driver("lattice_launches", "pinned")
