@@ -76,6 +76,9 @@ Layout3 layout_of(const lbm3d_config& c, int rows_per_tile, int tile_waves) {
     return L;
 }
 
+// Pieces of `size` that cover n.
+int64_t parts(int64_t n, int64_t size) { return (n + size - 1) / size; }
+
 struct Status3 {
     int code;
     std::string msg;
@@ -121,8 +124,7 @@ struct lbm3d_ctx {
     // 2670 / 1887; 512^3 FP16-SR 1464 / 1338, BF16-SR 1493 / 1378 with the
     // window kept in 16 bits and column-and-row rounding words)
     void set_default_fuse() {
-        const int64_t tiles = (int64_t)((cfg.nx + kPairW3 - 1) / kPairW3) * ((cfg.ny + kPairYO - 1) / kPairYO) *
-                              ((cfg.nz + shape.zchunk - 1) / shape.zchunk);
+        const int64_t tiles = parts(cfg.nx, kPairW3) * parts(cfg.ny, kPairYO) * parts(cfg.nz, shape.zchunk);
         fuse = tiles >= kPairMinTiles ? 2 : 1;
     }
     bool zauto = true;           // z ranges by z_range() (no launch shape was set)
@@ -141,17 +143,20 @@ struct lbm3d_ctx {
         int64_t rounds, cost;    // rounds of kZBlocks blocks; plane times
     };
     // Columns of xo x yo nodes, `halo` extra planes per range, and the percentage
-    // of the cost at 32 planes that a range has to stay below to replace it.
+    // of the cost at 32 planes that a range has to stay below to replace it.  At
+    // most kMostRanges ranges are tried: four full rounds of a single column, so
+    // more of them have nothing left to fill.
+    static constexpr int64_t kMostRanges = 1024;
     static Range z_range(const lbm3d_config& c, int xo, int yo, int halo, int percent) {
-        const int64_t cols = (int64_t)((c.nx + xo - 1) / xo) * ((c.ny + yo - 1) / yo);
-        auto at = [&](int zc) {
-            const int64_t r = (cols * ((c.nz + zc - 1) / zc) + kZBlocks - 1) / kZBlocks;
-            return Range{zc, r, r * (zc + halo)};
+        const int64_t cols = parts(c.nx, xo) * parts(c.ny, yo);
+        auto at = [&](int64_t zc) {
+            const int64_t r = parts(cols * parts(c.nz, zc), kZBlocks);
+            return Range{(int)zc, r, r * (zc + halo)};
         };
         Range best = at(std::min(32, (int)c.nz));
         int64_t least = best.cost * percent / 100;
-        for (int k = 1; k <= (c.nz + 7) / 8; ++k) {
-            const Range r = at((c.nz + k - 1) / k);
+        for (int64_t k = 1; k <= std::min(parts(c.nz, 8), kMostRanges); ++k) {
+            const Range r = at(parts(c.nz, k));
             if (r.cost < least) {
                 least = r.cost;
                 best = r;
@@ -159,9 +164,12 @@ struct lbm3d_ctx {
         }
         return best;
     }
-    Range pair_range() const { return z_range(cfg, kPairW3, kPairYO, 4, cfg.storage == LBM_F32 ? 94 : 100); }
-    Range deep_range() const { return z_range(cfg, kDeepXO, kDeepYO, 2 * kDeepSteps, 97); }
-    int zrange() const { return zauto ? pair_range().planes : shape.zchunk; }
+    Range pair_range{}, deep_range{};   // of the box; the search is not for every call (set_ranges)
+    void set_ranges() {
+        pair_range = z_range(cfg, kPairW3, kPairYO, 4, cfg.storage == LBM_F32 ? 94 : 100);
+        deep_range = z_range(cfg, kDeepXO, kDeepYO, 2 * kDeepSteps, 97);
+    }
+    int zrange() const { return zauto ? pair_range.planes : shape.zchunk; }
     bool fauto = true;           // steps per launch chosen here (no explicit setting)
     // Three steps per launch (FP32 only; the same bits) instead of two, where
     // neither the launch shape nor the steps per launch were set.  A plane
@@ -175,8 +183,7 @@ struct lbm3d_ctx {
     // one round 256^3 240 / 253, 191 x 179 x 282 142 / 146, 192^3 103 / 119.
     bool deep_pays() const {
         if (cfg.storage != LBM_F32 || !deep_fits(L.g)) return false;
-        const Range p = pair_range();
-        return p.rounds >= 2 && deep_range().cost * 100 < p.cost * 73;
+        return pair_range.rounds >= 2 && deep_range.cost * 100 < pair_range.cost * 73;
     }
     bool deep() const { return fuse == 2 && fauto && zauto && deep_pays(); }
     double tau = 0, beta = 1, s = 1, cv = 1;
@@ -269,6 +276,7 @@ int lbm3d_create(const lbm3d_config* cfg, lbm3d_handle* out) {
     h->shape = cfg->layout == LBM_LAYOUT_PLANES ? lbm3d_launch_shape{4, 1, 0, 1, 32}
                                                 : lbm3d_launch_shape{4, 0, 0, 1, 32};
     h->L = layout_of(*cfg, h->shape.rows_per_tile, h->shape.tile_waves);
+    h->set_ranges();
     h->set_default_fuse();
     derive(h);
     if (!(cfg->flags & LBM_FLAG_EXTERNAL_MEMORY)) {
@@ -380,16 +388,16 @@ int lbm3d_step(lbm3d_handle h, int64_t nsteps) {
     p.xcd_remap = 1;
     p.nontemporal = a.nontemporal;
     p.zchunk = h->zrange();
-    p.ptx = (uint32_t)((h->cfg.nx + kPairW3 - 1) / kPairW3);
-    p.pty = (uint32_t)((h->cfg.ny + kPairYO - 1) / kPairYO);
-    p.ptz = (uint32_t)((h->cfg.nz + p.zchunk - 1) / p.zchunk);
+    p.ptx = (uint32_t)parts(h->cfg.nx, kPairW3);
+    p.pty = (uint32_t)parts(h->cfg.ny, kPairYO);
+    p.ptz = (uint32_t)parts(h->cfg.nz, p.zchunk);
     p.ntiles = p.ptx * p.pty * p.ptz;
     t = p;
     const bool deep = h->deep();
-    t.zchunk = h->deep_range().planes;
-    t.ptx = (uint32_t)((h->cfg.nx + kDeepXO - 1) / kDeepXO);
-    t.pty = (uint32_t)((h->cfg.ny + kDeepYO - 1) / kDeepYO);
-    t.ptz = (uint32_t)((h->cfg.nz + t.zchunk - 1) / t.zchunk);
+    t.zchunk = h->deep_range.planes;
+    t.ptx = (uint32_t)parts(h->cfg.nx, kDeepXO);
+    t.pty = (uint32_t)parts(h->cfg.ny, kDeepYO);
+    t.ptz = (uint32_t)parts(h->cfg.nz, t.zchunk);
     t.ntiles = t.ptx * t.pty * t.ptz;
     for (int64_t k = 0; k < nsteps;) {
         const int64_t left = nsteps - k;
@@ -601,7 +609,7 @@ int lbm3d_autotune(lbm3d_handle h, int32_t steps, char* report, size_t report_le
     std::string prep;
     steps += steps & 1;
     bool best_deep = false;
-    const int zdef = h->pair_range().planes;
+    const int zdef = h->pair_range.planes;
     for (int cand = 0; cand < 5; ++cand) {
         const int zc = cand < 3 ? 16 << cand : zdef;
         if (cand == 4) {

@@ -1,0 +1,79 @@
+// What the D3Q14 host runtime launches, recorded on a host without a GPU (see
+// lattice_launches.cpp).  The first argument names the check.
+#include "hip_stub.h"
+#include "d3q14_runtime.cpp"
+
+#include <chrono>
+#include <vector>
+
+// ------------------------------------------------------------------ recorders
+
+struct Launch {
+    int steps, zchunk;
+};
+static std::vector<Launch> launches;
+
+namespace plbm3 {
+hipError_t launch_step(int, int, const StepArgs&, hipStream_t) { return launches.push_back({1, 0}), hipSuccess; }
+hipError_t launch_pair(int, int, int, const PairArgs& a, hipStream_t) {
+    return launches.push_back({2, a.zchunk}), hipSuccess;
+}
+hipError_t launch_triple(int, const PairArgs& a, hipStream_t) { return launches.push_back({3, a.zchunk}), hipSuccess; }
+hipError_t launch_init(int, const Geometry&, void*, const double*, const double*, const double*, const double*, double,
+                       double, double, double, hipStream_t) { return hipSuccess; }
+hipError_t launch_moments(int, const Geometry&, const void*, double, double, double*, double*, double*, double*,
+                          hipStream_t) { return hipSuccess; }
+hipError_t launch_sample(int, const Geometry&, const void*, double, double, const int64_t*, int64_t, double*,
+                         hipStream_t) { return hipSuccess; }
+int totals_blocks(const Geometry&) { return 1; }
+hipError_t launch_totals(int, const Geometry&, const void*, double*, double*, hipStream_t) { return hipSuccess; }
+hipError_t launch_fill(void*, size_t, uint32_t, hipStream_t) { return hipSuccess; }
+}
+
+static lbm3d_config config(int nx, int ny, int nz, int storage = LBM_F32) {
+    lbm3d_config c;
+    std::memset(&c, 0, sizeof c);
+    c.nx = nx;
+    c.ny = ny;
+    c.nz = nz;
+    c.storage = storage;
+    c.tau_n = 0.6;
+    c.tau_r = 5.0;
+    c.t0 = 1.0;
+    c.scale = 1.0;
+    return c;
+}
+
+static lbm3d_handle make(int nx, int ny, int nz, int storage = LBM_F32) {
+    const lbm3d_config c = config(nx, ny, nz, storage);
+    lbm3d_handle h = nullptr;
+    expect(lbm3d_create(&c, &h) == LBM_OK, "create");
+    static const double field = 1.0;
+    expect(lbm3d_init(h, &field, nullptr, nullptr, nullptr, 1) == LBM_OK, "init");
+    return h;
+}
+
+// The z ranges are searched once per box, not on every call, and over a bounded
+// number of candidates.
+static void ranges() {
+    lbm3d_handle h = make(1, 1, 1000000);
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int k = 0; k < 1000; ++k) expect(lbm3d_step(h, k & 1) == LBM_OK, "step");
+    const double us = std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count() / 1000;
+    std::printf("a step call on a million planes: %.2f us\n", us);
+    expect(us < 50.0, "host time of a step call");
+    lbm3d_destroy(h);
+    // the most planes: no overflow, and no long search at creation
+    lbm3d_config c = config(1, 1, INT32_MAX);
+    c.flags = LBM_FLAG_EXTERNAL_MEMORY;
+    expect(lbm3d_create(&c, &h) == LBM_OK && h->zrange() >= 1, "a column of 2^31 - 1 planes");
+    lbm3d_destroy(h);
+}
+
+int main(int argc, char** argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "ranges") ranges();
+    else expect(false, "unknown check");
+    std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
+    return failures ? 1 : 0;
+}

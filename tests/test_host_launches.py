@@ -60,3 +60,8 @@ def test_new_handles_pin_no_memory_without_use(driver):
     """lbm_create pins host memory only for handles with many check records;
     lbm_last_check never allocates."""
     driver("lattice_launches", "pinned")
+
+
+def test_z_ranges_are_searched_once(driver):
+    """Step calls on boxes of many planes cost no search of z ranges."""
+    driver("box_launches", "ranges")
