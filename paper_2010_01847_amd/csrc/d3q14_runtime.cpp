@@ -134,14 +134,20 @@ struct lbm3d_ctx {
     // range that makes that least fills the last round.  Measured (us per
     // step, range 32 / this one): 301 x 211 x 163 BF16 152 / 125 (24 planes),
     // FP32 211 / 186; 192^3 99.8 / 77.2 (48) and 125 / 99.6; 130 x 500 x 300
-    // 273 / 233 (150) and 389 / 353; 512^3 BF16 1309 / 1251 (57).  FP32 keeps
-    // 32 planes unless the count falls by 6%: 512^3 runs 1879 us per step at
-    // 32 and 1938 at 57 (5% fewer plane times, but the halo planes of blocks
-    // further apart in z miss the caches).
+    // 273 / 233 (150) and 389 / 353; 512^3 BF16 1309 / 1251 (57).  FP32 takes the
+    // range only where the count falls clearly (fp32_percent), else 32 planes: in
+    // one round of blocks by 6%, in several by 9% (200 x 160 x 256, 29 planes in
+    // two rounds, 92% of the count: 139 / 145; 512^3, 57 planes, 95%: 1879 / 1938)
+    // and by 17% for ranges of more than 64 planes, where blocks on far ranges
+    // lose step with their neighbours: 23 boxes of 83 to 92% of the count ran in
+    // 0.885 to 1.093 of the time (531 x 498 x 240, 120 planes: 902 / 952; timings of
+    // one and the same kernel vary by up to a tenth between allocations of such
+    // boxes), 73 others within the limits in 0.91 on average.
     struct Range {
         int planes;              // per block
         int64_t rounds, cost;    // rounds of kZBlocks blocks; plane times
     };
+    static int fp32_percent(const Range& r) { return r.rounds < 2 ? 94 : (r.planes > 64 ? 83 : 91); }
     // Columns of xo x yo nodes, `halo` extra planes per range, and the percentage
     // of the cost at 32 planes that a range has to stay below to replace it.  At
     // most kMostRanges ranges are tried: four full rounds of a single column, so
@@ -164,9 +170,17 @@ struct lbm3d_ctx {
         }
         return best;
     }
-    Range pair_range{}, deep_range{};   // of the box; the search is not for every call (set_ranges)
+    // of the box; the search is not for every call (set_ranges).  pair_least: the
+    // two-step range of the least count, which the count of three steps is
+    // compared with (deep_pays).
+    Range pair_range{}, pair_least{}, deep_range{};
     void set_ranges() {
-        pair_range = z_range(cfg, kPairW3, kPairYO, 4, cfg.storage == LBM_F32 ? 94 : 100);
+        pair_least = z_range(cfg, kPairW3, kPairYO, 4, cfg.storage == LBM_F32 ? 94 : 100);
+        pair_range = pair_least;
+        if (cfg.storage == LBM_F32) {
+            const Range at32 = z_range(cfg, kPairW3, kPairYO, 4, 0);
+            if (pair_least.cost * 100 >= at32.cost * fp32_percent(pair_least)) pair_range = at32;
+        }
         deep_range = z_range(cfg, kDeepXO, kDeepYO, 2 * kDeepSteps, 97);
     }
     int zrange() const { return zauto ? pair_range.planes : shape.zchunk; }
@@ -183,7 +197,7 @@ struct lbm3d_ctx {
     // one round 256^3 240 / 253, 191 x 179 x 282 142 / 146, 192^3 103 / 119.
     bool deep_pays() const {
         if (cfg.storage != LBM_F32 || !deep_fits(L.g)) return false;
-        return pair_range.rounds >= 2 && deep_range.cost * 100 < pair_range.cost * 73;
+        return pair_least.rounds >= 2 && deep_range.cost * 100 < pair_least.cost * 73;
     }
     bool deep() const { return fuse == 2 && fauto && zauto && deep_pays(); }
     double tau = 0, beta = 1, s = 1, cv = 1;

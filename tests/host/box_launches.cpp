@@ -70,9 +70,31 @@ static void ranges() {
     lbm3d_destroy(h);
 }
 
+// The z ranges of the two-step kernel: filled rounds, but FP32 keeps 32 planes
+// where the gain is small or the ranges are long.
+static void planes() {
+    struct Case {
+        int nx, ny, nz, storage, planes;
+    };
+    for (const Case& c : {Case{301, 211, 163, LBM_BF16, 24}, Case{301, 211, 163, LBM_F32, 24}, Case{192, 192, 192, LBM_F32, 48},
+                          Case{130, 500, 300, LBM_F32, 150}, Case{512, 512, 512, LBM_BF16, 57}, Case{512, 512, 512, LBM_F32, 32},
+                          Case{200, 160, 256, LBM_F32, 32}, Case{200, 160, 256, LBM_F16, 29}, Case{531, 498, 240, LBM_F32, 32},
+                          Case{202, 436, 661, LBM_F32, 32}, Case{132, 526, 630, LBM_F32, 32}, Case{122, 213, 237, LBM_F32, 27}}) {
+        lbm3d_handle h = make(c.nx, c.ny, c.nz, c.storage);
+        expect(lbm3d_set_step_fusion(h, 2) == LBM_OK, "step fusion");
+        launches.clear();
+        expect(lbm3d_step(h, 2) == LBM_OK, "step");
+        const bool ok = launches.size() == 1 && launches[0].steps == 2 && launches[0].zchunk == c.planes;
+        if (!ok) std::printf("%d x %d x %d: %d planes\n", c.nx, c.ny, c.nz, launches.empty() ? 0 : launches[0].zchunk);
+        expect(ok, "planes of a range");
+        lbm3d_destroy(h);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "ranges") ranges();
+    else if (what == "planes") planes();
     else expect(false, "unknown check");
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -65,3 +65,8 @@ def test_new_handles_pin_no_memory_without_use(driver):
 def test_z_ranges_are_searched_once(driver):
     """Step calls on boxes of many planes cost no search of z ranges."""
     driver("box_launches", "ranges")
+
+
+def test_z_ranges_by_box(driver):
+    """The planes per block that a new handle takes for two steps per launch."""
+    driver("box_launches", "planes")
