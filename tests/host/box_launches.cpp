@@ -91,10 +91,29 @@ static void planes() {
     }
 }
 
+// The boxes that the GPU tests of three steps per launch compare with single
+// steps do take three, in the calls that they make.
+static void triples() {
+    const int boxes[][3] = {{144, 260, 186}, {498, 109, 118}, {102, 394, 285}, {47, 800, 171}, {512, 512, 512}};
+    for (auto& b : boxes) {
+        lbm3d_handle h = make(b[0], b[1], b[2]);
+        std::string got;
+        for (int n : {3, 1, 4, 2, 5, 7}) {
+            launches.clear();
+            expect(lbm3d_step(h, n) == LBM_OK, "step");
+            for (const Launch& l : launches) got += std::to_string(l.steps);
+            got += " ";
+        }
+        expect(got == "3 1 22 2 32 322 ", "launches of a box that takes three steps");
+        lbm3d_destroy(h);
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "ranges") ranges();
     else if (what == "planes") planes();
+    else if (what == "triples") triples();
     else expect(false, "unknown check");
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -307,6 +307,30 @@ static void pinned() {
     }
 }
 
+// The forms that the GPU tests of the block kernels mean to run.
+static void forms() {
+    struct Case {
+        int nx, ny, storage, kind, rows, waves, wx, wy, count = 1;   // 0: any
+    };
+    const Case cases[] = {
+        {64, 16, LBM_F32, kBlockWhole, 1, 16, 0, 0}, {32, 32, LBM_F32, kBlockWhole, 1, 16, 0, 0},
+        {30, 20, LBM_F32, kBlockWhole, 1, 10, 0, 0}, {41, 25, LBM_F32, kBlockWhole, 2, 9, 0, 0},
+        {64, 32, LBM_F32, kBlockWhole, 2, 16, 0, 0, 600}, {20, 20, LBM_F32, kBlockWhole, 1, 7, 0, 0, 2500},
+        {131, 67, LBM_BF16, kBlockPatch, 1, 16, 32, 32}, {1189, 4, LBM_F32, kBlockPatch, 1, 13, 28, 28},
+        {13, 9651, LBM_F16, kBlockPatch, 1, 13, 28, 28}, {4758, 4, LBM_F32, kBlockPatch, 1, 12, 32, 24},
+        {9, 16408, LBM_F32, kBlockPatch, 1, 9, 24, 24}, {401, 301, LBM_F16, kBlockTiles, 0, 0, 0, 0},
+        {1500, 1400, LBM_F32, kBlockTiles, 4, 12, 0, 0},
+    };
+    for (const Case& c : cases) {
+        const BlockPlan p = block_plan(std::vector<lbm_instance>((size_t)c.count, inst(c.nx, c.ny)), c.storage);
+        const bool ok = p.kind == c.kind && (!c.rows || p.rows == c.rows) && (!c.waves || p.waves == c.waves) &&
+                        p.wx == c.wx && p.wy == c.wy;
+        if (!ok) std::printf("%d x %d: kind %d, rows %d, %d wavefronts, %d x %d\n", c.nx, c.ny, p.kind, p.rows, p.waves,
+                             p.wx, p.wy);
+        expect(ok, "form");
+    }
+}
+
 int main(int argc, char** argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "streams") streams();
@@ -314,6 +338,7 @@ int main(int argc, char** argv) {
     else if (what == "plans") plans();
     else if (what == "short_runs") short_runs();
     else if (what == "pinned") pinned();
+    else if (what == "forms") forms();
     else expect(false, "unknown check");
     std::printf("%s: %s\n", what.c_str(), failures ? "FAILED" : "ok");
     return failures ? 1 : 0;

@@ -70,3 +70,13 @@ def test_z_ranges_are_searched_once(driver):
 def test_z_ranges_by_box(driver):
     """The planes per block that a new handle takes for two steps per launch."""
     driver("box_launches", "planes")
+
+
+def test_forms_of_the_gpu_tests(driver):
+    """The GPU tests of the block kernels run the forms they name."""
+    driver("lattice_launches", "forms")
+
+
+def test_boxes_of_the_gpu_tests_take_three_steps(driver):
+    """The GPU tests of three steps per launch run them."""
+    driver("box_launches", "triples")
