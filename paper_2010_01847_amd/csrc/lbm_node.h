@@ -400,16 +400,6 @@ __device__ __forceinline__ float from_right(float v, float edge) {
     return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(edge), __float_as_int(v), 0x130, 0xf, 0xf, false));
 }
 
-// Orders the wavefront's LDS accesses before and after it, for values that one
-// lane writes and another reads (the compiler sees one lane only, and may
-// reorder accesses that never meet within it).  No instruction: a wavefront's
-// LDS accesses execute in the order they are issued.
-__device__ __forceinline__ void lane_order() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // v rounded to S: to nearest, or (SR, 16-bit) stochastically with 16 random bits.
 template <class S, int SR>
 __device__ __forceinline__ S round_to(float v, uint32_t r16) {
