@@ -1428,22 +1428,32 @@ static Next next_march(const lbm_ctx* h, int64_t m, int64_t last) {
 // Up to how many steps a handle in the block kernels leaves to the launches it
 // would have without them.  A block launch loads whole windows and stores the
 // lattice however few its steps are, and one that ends a call also stores the
-// state before (keep_prev) or has it replayed by a readout.  Where the marching
-// kernel is there (handles of kFuseMinStrips strips or more), it or a single
-// step takes few steps faster; FP32 us per call, march / block: two steps 1500 x
-// 1400 35.9 / 36.1, 1700 x 1500 35.5 / 43.0, 2048^2 49 / 111; four steps 1500 x
-// 1400 53 / 42, 1700 x 1500 53 / 49, 2048^2 66 / 112, even without the state
-// before 67; FP32 stochastic and 16-bit rounding every step reach that point
-// later: FP32-SR four steps 2048^2 160 / 138, FP16-SR two 1700 x 1500 40.6 /
-// 35.6, 2048^2 49.6 / 54.8, three 67.5 / 69.7.  Without it, two steps run as
-// single ones: 512^2 8.9 / 9.6, 401 x 301 7.1 / 7.3, 2 x 100000 44 / 62, but 128
-// x 64 6.0 / 4.8 and whole lattices always faster (1000 of 41 x 25 60 / 41).
+// state before (keep_prev) or has it replayed by a readout.
+// Where the marching kernel is there (handles of kFuseMinStrips strips or more),
+// it takes few steps faster.  FP32 us per call, march / block: two steps 1500 x
+// 1400 34.5 / 36.0 (with a readout 86 / 67), 1700 x 1500 35.5 / 43.0, 2048^2 49 /
+// 111 (170 / 162); four steps 1500 x 1400 53 / 42, 1700 x 1500 53 / 49, 2048^2 66 /
+// 112, even without the state before 67.  FP32 stochastic and 16-bit storage
+// rounding every step reach that point later: FP32-SR four steps 2048^2 160 / 138,
+// FP16-SR two 1700 x 1500 40.6 / 35.6, 2048^2 49.6 / 54.8, three 67.5 / 69.7.
+// Elsewhere two steps run as single ones from 100,000 nodes on (single / block:
+// 512^2 8.8 / 9.5, 512 x 400 FP32-SR 10.8 / 13.8, 1024 x 1000 F16_SPLIT 19.6 /
+// 20.7, 50000 x 3 9.3 / 11.8, but 128 x 64 6.0 / 4.8), except several instances
+// (50 of 100 x 40 43 / 34, on two streams), rows that leave lanes idle (16 x 20000
+// 34 / 17, 100 x 3000 11.6 / 10.1), and FP32 and FP16-SR from 340,000 nodes on (1024
+// x 700 17.0 / 15.1, 16.6 / 15.7; 640^2 11.6 / 11.1, 13.0 / 10.7; but 30000 x 16
+// 12.8 / 15.5).
 static int few_steps(const lbm_ctx* h) {
     if (h->bplan.kind == kBlockWhole) return 1;
-    if (h->fuse < 2) return h->L.nodes >= 100000 ? 2 : 1;
+    if (h->fuse < 2) {
+        const lbm_instance& in = h->inst[0];
+        const int64_t n = h->L.nodes, lanes = (in.nx + 63) / 64 * (int64_t)64 * in.ny;
+        if (h->inst.size() > 1 || n < 100000 || n * 20 < lanes * 17) return 1;
+        const bool wide = std::min(in.nx, in.ny) >= 64 && h->storage == (h->sr ? LBM_F16 : LBM_F32);
+        return wide && n >= 340000 ? 1 : 2;
+    }
     if (h->storage != LBM_F32) return h->L.buf_bytes > (size_t)58 << 20 ? 3 : 1;
-    if (h->sr) return 1;
-    return h->L.buf_bytes > (size_t)73 << 20 ? 4 : 2;
+    return h->L.buf_bytes > (size_t)73 << 20 && !h->sr ? 4 : 1;
 }
 
 // The launch that starts at step m in a sequence of steps that ends at step
@@ -1492,14 +1502,21 @@ static Next plan_next(const lbm_ctx* h, int64_t m, int64_t last) {
     return {kBlock, k, k == r && to_check && !rest ? kEndCheck : kEndPlain};
 }
 
-// Whether a block launch of k steps that ends a call (or a captured chunk) also
-// stores the state of the step before its last, which readouts start from: where
-// the three buffers stay in the 256 MB last-level cache the store costs less
-// than the replay of k - 1 steps by the first readout (FP32, calls of seven steps
-// without readout, us, not stored / stored: 512^2 14.6 / 15.7, 1024^2 35.7 / 36.9,
-// 1700 x 1500 64 / 67, but 2048^2 101 / 117 and of two steps 52 / 111), and so it
-// does after many steps (whole lattices).
-static bool keep_prev(const lbm_ctx* h, int k) { return 3 * h->L.buf_bytes <= (size_t)256 << 20 || k > 16; }
+// Whether the block launch of k steps that ends a call (or captured chunk) of
+// `steps` steps also stores the state of the step before its last, which readouts
+// start from.  The store costs less than the replay of the launch's other steps
+// by the first readout, but every call pays it: where the three buffers stay in
+// the 256 MB last-level cache it is small (FP32, calls of seven steps without
+// readout, us, not stored / stored: 512^2 14.6 / 15.7, 1024^2 35.7 / 36.9, 1700 x
+// 1500 64 / 67); beyond it, it is smallest in launches of the most steps (2048^2,
+// without block kernels / not stored / stored: seven steps 115 / 101 / 117, with a
+// readout 269 / 250 / 169; five steps 82 / 78 / 112) and small in calls of three
+// launches or more (28 steps 459 / 403 / 411, with a readout 614 / 553 / 469).
+static bool keep_prev(const lbm_ctx* h, int k, int64_t steps) {
+    if (3 * h->L.buf_bytes <= (size_t)256 << 20) return true;
+    const int most = h->bplan.kind == kBlockWhole ? 8 : h->bplan.halo;
+    return k >= most || steps >= 3 * most;
+}
 
 // The plan's part of a block launch's arguments, for k steps.
 static void block_args(const lbm_ctx* h, int k, BlockArgs* b) {
@@ -1586,7 +1603,7 @@ static int capture(lbm_ctx* h, int par) {
         const Next next = plan_next(h, s, C);
         const int k = next.k;
         const bool block = next.kind == kBlock;
-        const bool keep = block && s + k - 1 == C && keep_prev(h, k);
+        const bool keep = block && s + k - 1 == C && keep_prev(h, k, C);
         tail = lbm_ctx::Tail();
         tail_flip = flips & 1;
         for (int p = 0; p < np && rc == LBM_OK; ++p) {
@@ -1661,7 +1678,7 @@ static int step_loop(lbm_ctx* h, int64_t nsteps, bool multi) {
             sched == LBM_SCHED_PER_INSTANCE ? Next{kSingle, 1, kEndPlain} : plan_next(h, m, h->steps + left);
         const int k = next.k;
         const bool block = next.kind == kBlock;
-        const bool keep = block && k == left && keep_prev(h, k);
+        const bool keep = block && k == left && keep_prev(h, k, nsteps);
         h->tail = lbm_ctx::Tail();
         if (k >= 2) {
             for (int p = 0; p < np; ++p) {

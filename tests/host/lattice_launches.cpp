@@ -244,14 +244,17 @@ static void short_runs() {
         const char *two, *three, *four, *seven;  // kinds launched by calls of that many steps
     };
     const int every = LBM_FLAG_ROUND_EVERY_STEP, sr = LBM_FLAG_STOCHASTIC_ROUNDING;
-    for (const Case& c : {Case{128, 64, LBM_F32, 0, "2", "2", "2", "2"}, Case{512, 512, LBM_F32, 0, "00", "2", "2", "2"},
-                          Case{1000, 1000, LBM_F16, 0, "00", "2", "2", "2"},
-                          Case{1500, 1400, LBM_F32, 0, "1+0", "2", "2", "2"},
-                          Case{1700, 1500, LBM_F32, 0, "1+0", "1+1", "1+1", "2"},
-                          Case{2048, 2048, LBM_F32, 0, "1+0", "1+1", "1+1", "2+2"},
-                          Case{2048, 2048, LBM_F32, sr, "2+2", "2+2", "2+2", "2+2"},
-                          Case{2048, 2048, LBM_F16, every, "1+0", "1+1", "2", "2"},
-                          Case{1500, 1400, LBM_F16, every, "2", "2", "2", "2"}}) {
+    const Case cases[] = {
+        {128, 64, LBM_F32, 0, "2", "2", "2", "2"},          {512, 512, LBM_F32, 0, "00", "2", "2", "2"},
+        {640, 640, LBM_F32, 0, "2", "2", "2", "2"},         {1000, 1000, LBM_F32, sr, "00", "2", "2", "2"},
+        {1024, 1000, LBM_F16, 0, "00", "2", "2", "2"},      {1024, 1000, LBM_F16, sr, "2", "2", "2", "2"},
+        {16, 20000, LBM_F32, sr, "2", "2", "2", "22"},      {1500, 1400, LBM_F32, 0, "2", "2", "2", "2"},
+        {1700, 1500, LBM_F32, 0, "1+0", "1+1", "1+1", "2"}, {2048, 2048, LBM_F32, 0, "1+0", "1+1", "1+1", "2"},
+        {2048, 2048, LBM_F32, sr, "2+2", "2+2", "2+2", "2"}, {2048, 2048, LBM_F16, every, "1+0", "1+1", "2", "2"},
+        {1500, 1400, LBM_F16, every, "2", "2", "2", "2"},   {401, 301, LBM_F32, sr, "00", "2", "2", "2"},
+        {30000, 16, LBM_F32, 0, "00", "2", "2", "2"},       {100, 3000, LBM_F16, 0, "2", "2", "2", "2"},
+    };
+    for (const Case& c : cases) {
         lbm_handle h = make({inst(c.nx, c.ny)}, c.storage, -1, c.flags);
         same(kinds(h, 2), c.two, "two steps");
         same(kinds(h, 3), c.three, "three steps");
@@ -259,6 +262,12 @@ static void short_runs() {
         same(kinds(h, 7), c.seven, "seven steps");
         lbm_destroy(h);
     }
+    // the state before the last step of a call of three full launches is stored
+    lbm_handle big = make({inst(2048, 2048)}, LBM_F32, -1);
+    same(kinds(big, 6), "2+2", "six steps");
+    same(kinds(big, 20), "222+2", "20 steps");
+    same(kinds(big, 21), "222", "21 steps");
+    lbm_destroy(big);
     // a segment's last launches up to a check step
     for (int n : {2000, 1500, 1000, 700})
         for (int flags : {0, sr})
@@ -277,6 +286,7 @@ static void short_runs() {
     lbm_handle h = make(std::vector<lbm_instance>(2500, inst(20, 20)), LBM_F32, -1);
     same(kinds(h, 100), "22", "100 steps of many lattices");
     same(kinds(h, 7), "22+2", "seven steps of many lattices");
+    same(kinds(h, 8), "22", "eight steps of many lattices");
     lbm_destroy(h);
     // tuned to the block kernels, a handle keeps fused launches for few steps
     h = make({inst(2048, 2048)}, LBM_F32, -1, 0, false);
@@ -284,7 +294,7 @@ static void short_runs() {
     expect(lbm_autotune(h, 4, nullptr, 0) == LBM_OK, "autotune");
     cost_us = nullptr;
     start(h, 1);
-    same(kinds(h, 7), "2+2", "seven steps, tuned");
+    same(kinds(h, 6), "2+2", "six steps, tuned");
     same(kinds(h, 3), "1+1", "three steps, tuned");
     lbm_destroy(h);
 }
