@@ -151,11 +151,11 @@ enum FusedEnd { kEndPlain = 0, kEndSnap = 1, kEndCheck = 2, kEndMoments = 3 };
 // the storage type (FusedRounding): rounding every step, four steps per
 // launch were the fastest (FP16-SR 743, F16_SPLIT 819 us per launch on
 // 8192^2); rounding the last one, six.  Chunks of kMarchRows rows, or kTallRows
-// or kShortRows in large and small 16-bit handles (march_rows_of).
+// kMidRows or kShortRows in large and small 16-bit handles (march_rows_of).
 constexpr int kMarchRows = 32;
-constexpr int kTallRows = 64, kTallSteps = 5, kShortRows = 16;
-// One round of strips.
-constexpr int64_t kShortStrips = 256 * 4 * 5;
+constexpr int kTallRows = 64, kTallSteps = 5, kShortRows = 16, kMidRows = 24;
+// One round of strips at five and at four wavefronts per SIMD.
+constexpr int64_t kShortStrips = 256 * 4 * 5, kMidStrips = 256 * 4 * 4;
 // Three rounds of strips at five wavefronts per SIMD.
 constexpr int64_t kTallStrips = 3 * 256 * 4 * 5;
 // Elements between direction runs in the chunked layout (64-node segments).

@@ -256,6 +256,14 @@ int64_t fused_tiles_x(const lbm_instance& in, int storage) {
 // lasts as long as one strip.  FP16-SR, us per step, 32 / 16 rows: 1200 x 1400
 // (2112 strips of 16 rows) 12.8 / 9.3, 1800 x 1600 (3500) 13.0 / 10.9, 4000 x 900
 // (4389) 15.4 / 12.5, on the other side 2200 x 2000 (5375) 15.5 / 15.6.
+// kMidRows where theirs fit in one round at four wavefronts per SIMD, as many as
+// every kernel holds (kMidStrips).  With 32 rows these handles leave a third of
+// the chip idle, and the LDS delay lines, made for five wavefronts, cost them 1 to
+// 4% (us per 96 steps, delay lines in registers and 32 rows / in LDS, 32 / this):
+// 837 x 5577 (3961 strips of 24 rows) FP16-SR 1441 / 1475 / 1374, BF16-SPLIT-SR
+// 1618 / 1675 / 1552, 2200 x 2000 (3696) BF16-SR 1450 / 1494 / 1386; up to a round
+// of five (2600 x 2300, 4800) six steps would gain 8% too, but BF16 launches of
+// four steps, which hold four wavefronts, lose 6%.
 int64_t strips_of(const std::vector<lbm_instance>& v, int storage, int rows) {
     int64_t n = 0;
     for (auto& in : v) n += fused_tiles_x(in, storage) * (int64_t)((in.ny + rows - 1) / rows);
@@ -264,6 +272,7 @@ int64_t strips_of(const std::vector<lbm_instance>& v, int storage, int rows) {
 int march_rows_of(const std::vector<lbm_instance>& v, int storage, int every_step) {
     if (storage == LBM_F32 || every_step) return kMarchRows;
     if (strips_of(v, storage, kShortRows) <= kShortStrips) return kShortRows;
+    if (strips_of(v, storage, kMidRows) <= kMidStrips) return kMidRows;
     return strips_of(v, storage, kTallRows) >= kTallStrips ? kTallRows : kMarchRows;
 }
 

@@ -161,7 +161,7 @@ static void strips() {
         int nx, ny, few, many;   // rows per strip below kTallSteps steps, and from there on
     };
     for (const Size& s : {Size{8192, 8192, 32, 64}, Size{8192, 8222, 32, 64}, Size{2600, 2300, 32, 32},
-                          Size{1500, 1400, 16, 16}})
+                          Size{837, 5577, 24, 24}, Size{1500, 1400, 16, 16}})
         for (int storage : {LBM_F16, LBM_BF16_SPLIT})
             for (int how = 0; how < 3; ++how)
                 for (int k = 2; k <= fuse_max(storage); ++k) {

@@ -58,3 +58,25 @@ def test_changing_the_steps_per_launch(order):
         got.append(out)
     for one, many in zip(*got):
         assert all(torch.equal(a.expand_as(b), b) for a, b in zip(one, many))
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16_split"])
+def test_strips_of_24_rows(storage):
+    # 2 strips x 1875 chunks of 24 rows; one period runs in strips of 16
+    nx, ny, m = 59, 1000, 45
+    T = torch.from_numpy(W.random_field(nx, ny, 1e-3, 1.0, 9)).cuda()
+    got = []
+    for reps in (1, m, m + 40):     # 126, 5626 and 10626 strips of 16 rows: 16, 24 and 32 rows
+        lat = Lattice([instance_from_case(W.Case("mid", nx, ny * reps, 0.6, 7.0), 2.0 ** -19)], storage=storage,
+                      check_interval=0)
+        lat.set_step_fusion(6)
+        lat.init(0, T.repeat(reps, 1))
+        out = []
+        for n in (6, 5, 13, 2):
+            lat.step(n)
+            out.append([t.view(reps, ny, nx) for t in lat.moments_device(0)])
+        lat.close()
+        got.append(out)
+    for other in got[1:]:
+        for one, many in zip(got[0], other):
+            assert all(torch.equal(a.expand_as(b), b) for a, b in zip(one, many))
