@@ -160,10 +160,10 @@ int lbm3d_get_launch_shape(lbm3d_handle h, lbm3d_launch_shape* shape);
 /* Time every single-step tile shape (rows_per_tile x tile_waves) with and
  * without the XCD remap, then streaming stores on the fastest, then two steps
  * per launch over z ranges of 16, 32 and 64 planes, each with and without
- * streaming stores (and a new handle's own z range and steps per launch), for `steps` steps each (0 selects 20) on buffers filled
- * with a fixed pattern of moderate finite values; keep the fastest shape, z
- * range, store kind and steps per launch.  Must run before lbm3d_init (it
- * overwrites the buffers).  report, if not NULL, receives a JSON summary
+ * streaming stores (and a new handle's own z range and steps per launch), for
+ * `steps` steps each (0 selects 20) on buffers filled with a fixed pattern of
+ * moderate finite values; keep the fastest shape, z range, store kind and steps
+ * per launch.  Must run before lbm3d_init (it overwrites the buffers).  report, if not NULL, receives a JSON summary
  * ({"timings_us": [[rows, xcd, nt, tile_waves, us], ...], "best": [rows, xcd,
  * nt, tile_waves, single-step us], "pair_us_per_step": [[zchunk, nt, us],
  * ...], "zchunk": z, "steps_per_launch": 1 or 2, "launch_steps": 1, 2 or 3

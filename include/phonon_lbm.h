@@ -322,14 +322,15 @@ int lbm_set_wall_flux(lbm_handle h, int32_t inst, int32_t wall, double q0);
  * lbm_max_step_fusion gives the kind's most).  Default
  * for a new handle: that most when its instances hold at least 1024 strips of
  * the fused kernel in all (64 - 2 k columns by 32 rows each, k the most), so
- * that a fused launch fills the chip, else 1.  A new handle of up to 4.5
- * million nodes (16-bit storage: where the default is 1, or with
- * LBM_FLAG_ROUND_EVERY_STEP) advances several steps per launch in kernels that
- * hold the lattices on the chip, every step rounded as a stored one is: the
- * same bits as single steps, whatever this setting's default says.  Calling
- * this function or lbm_set_launch_shape selects the launches they describe
- * instead.  The per-instance schedule always issues single steps.  Drops captured graphs.  Errors: EINVAL (steps
- * < 1 or more than the handle's most). */
+ * that a fused launch fills the chip, else 1.  A new handle of up to 4.3
+ * million nodes whose lattices are not too thin (16-bit storage: where the
+ * default is 1, or with LBM_FLAG_ROUND_EVERY_STEP) advances several steps per
+ * launch in kernels that hold the lattices on the chip, where those are the
+ * faster, every step rounded as a stored one is: the same bits as single steps,
+ * whatever this setting's default says.  Calling this function or
+ * lbm_set_launch_shape selects the launches they describe instead.  The
+ * per-instance schedule always issues single steps.  Drops captured graphs.
+ * Errors: EINVAL (steps < 1 or more than the handle's most). */
 int lbm_set_step_fusion(lbm_handle h, int32_t steps);
 
 /* The current most time steps per launch; -1 for an invalid handle. */
@@ -383,11 +384,12 @@ int lbm_get_launch_shape(lbm_handle h, lbm_launch_shape* shape);
  * the fastest, then time fused launches of every number of steps up to the
  * storage kind's most against it and set the steps per launch
  * (lbm_set_step_fusion) to the fastest; the kernels that hold small lattices
- * on the chip are timed too and kept where they are faster (16-bit storage:
- * than single steps).  Must be called after
- * lbm_create and before lbm_init (it runs steps on scratch contents); each
- * candidate is timed over `steps` steps (0 = 20) with HIP events.  If the environment variable LBM_AUTOTUNE_CACHE
- * names a file, a result for the same device, storage and instance shapes is
+ * on the chip are timed too and kept where they are faster still.  16-bit
+ * storage that rounds the last step of a launch only keeps fused launches that
+ * beat single steps even so: those kernels round every step.  Must be called
+ * after lbm_create and before lbm_init (it runs steps on scratch contents); each
+ * candidate is timed over `steps` steps (0 = 20) with HIP events.  If the
+ * environment variable LBM_AUTOTUNE_CACHE names a file, a result for the same device, storage and instance shapes is
  * read from it instead of timing, and new results are appended to it.
  * report (may be NULL) receives a JSON summary of the timings.
  * Errors: ESTATE (already initialised), EHIP. */

@@ -25,8 +25,9 @@
 // costs 14 words of LDS per stage there, so three stages of it leave too few
 // output rows; here LDS holds only the rows that cross wavefronts, and two rows
 // per wavefront halve those (12 waves, 60 KB of LDS, all 168 VGPRs that three
-// waves per SIMD leave).  Bound by HBM and the caches (64 x 24 nodes loaded
-// for 58 x 18 stored): 512^3 runs 1716 us per step against 1884 in launches of
+// waves per SIMD leave; four of them spill in the chunked layout, ten in planes,
+// 14 and 19 with stochastic rounding).  Bound by HBM and the caches (64 x 24
+// nodes loaded for 58 x 18 stored): 512^3 runs 1716 us per step against 1884 in launches of
 // two and 2670 in single steps, on another card 1622 against 1745.  16-bit
 // storage stays with two steps: there this kernel's arithmetic costs more than
 // the traffic it saves (512^3 at two steps per launch 1391 .. 1450 against 1251

@@ -61,7 +61,8 @@ __device__ __forceinline__ bool x_walled(const InstDesc& d) { return d.bc_x == 1
 // few blocks per CU, by the windows' loads (one third of 1024 x 256's time) at
 // many.  Rows are worked through one by one: interleaving them (or holding the
 // steps in separate code for the last two) took 91-103 VGPRs instead of 73 and
-// ran 1024^2 in 5.3 us.
+// ran 1024^2 in 5.3 us.  Launches that end on a check step need 110-121 VGPRs for
+// the FP64 moments, so one block of 12 wavefronts runs per CU instead of two.
 template <class S, int SR, int SPLIT, int R, int END>
 __global__ __launch_bounds__(1024) void tile_kernel(BlockArgs b, int xcd, int nontemporal) {
     extern __shared__ float edges[];          // [2][waves][6][64]

@@ -524,7 +524,7 @@ hipError_t launch_plane_moments(const InstDesc* d_desc, int inst, const InstDesc
 
 // ------------------------------------------------------------------ K steps per launch, y-marching
 //
-// Temporal blocking without LDS or barriers: K time steps per pass over HBM.
+// Temporal blocking without barriers: K time steps per pass over HBM.
 // A wavefront owns a 64-column window (W = 64 - 2 KMAX output columns and a
 // KMAX-node halo on each side, periodic images) of a chunk of march_rows
 // output rows and marches along y.  Iteration `it` loads input row
@@ -533,14 +533,15 @@ hipError_t launch_plane_moments(const InstDesc* d_desc, int inst, const InstDesc
 // s..63-s (its pulls stay inside the window); stage K stores its output
 // lanes.  A node pulls direction i from row y - c_iy, so of a level's newest
 // row the c_y = -1 movers are used at once, the c_y = 0 movers one iteration
-// later and the c_y = +1 movers two iterations later (kept in registers), and
-// the x neighbours come from the adjacent lanes by DPP.  Per node and step the
-// arithmetic is the single-step kernels' (same functions, same order, same
-// random bits).  RM (FusedRounding) says which levels are rounded exactly as a
-// stored step: all of them (kRoundEvery, then the result equals K single steps
-// bit for bit), or for 16-bit storage only the last (kRoundLast), the others
-// keeping the FP32 result of the relaxation: the state a 16-bit launch leaves
-// in HBM then carries one rounding to 16 bits, not K.
+// later and the c_y = +1 movers two iterations later (kept in registers, in
+// launches of many steps partly in LDS: MarchForm), and the x neighbours come
+// from the adjacent lanes by DPP.  Per node and step the arithmetic is the
+// single-step kernels' (same functions, same order, same random bits).  RM
+// (FusedRounding) says which levels are rounded exactly as a stored step: all of
+// them (kRoundEvery, then the result equals K single steps bit for bit), or for
+// 16-bit storage only the last (kRoundLast), the others keeping the FP32 result
+// of the relaxation: the state a 16-bit launch leaves in HBM then carries one
+// rounding to 16 bits, not K.
 
 // K <= KMAX: the window geometry depends on KMAX only, so launches of fewer
 // steps (before a check step or at the end of a call) use the same tile table.
@@ -566,14 +567,15 @@ hipError_t launch_plane_moments(const InstDesc* d_desc, int inst, const InstDesc
 // In launches of many steps the first kDelayLevels levels keep their c_y = +1
 // movers (two rows of three values) in LDS, 1.5 KB per level and wavefront, the
 // others in registers.  These launches are bound by VALU issue, which more
-// wavefronts per SIMD fill better: 90-96 VGPRs instead of 114-128 allow five
-// instead of four, whose LDS (120 KB of a CU's 160) four levels leave room for.
+// wavefronts per SIMD fill better: 73-96 VGPRs (the stochastic split kinds spill
+// 4 to 7 of theirs at six steps) instead of 114-128 allow five instead of four,
+// whose LDS (120 KB of a CU's 160) four levels leave room for.
 // Reading a level back at the neighbouring lanes' addresses also saves its two
 // diagonal DPP pulls and six moves.  Measured (8192^2, us per step, all in
 // registers / this): FP16-SR 159.5 / 145.6, FP16 154.6 / 139.6, BF16-SR 163 /
 // 156, F16_SPLIT 167 / 153, BF16_SPLIT 168 / 154, FP32 179.4 / 177.2 (bound by
 // its HBM traffic there; 3000 x 2500: 27.3 / 23.9).  At four wavefronts per SIMD
-// the LDS form is 2% slower than registers; five levels leave LDS for four
+// the LDS form is 1 to 4% slower than registers (see kMidRows); five levels leave LDS for four
 // (FP16-SR 164); all five delayed movers of three levels 145.7, of two 163 (105
 // VGPRs).
 // Launches of fewer steps wait for memory, and more wavefronts in flight or LDS

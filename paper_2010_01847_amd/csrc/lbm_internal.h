@@ -145,8 +145,8 @@ enum FusedEnd { kEndPlain = 0, kEndSnap = 1, kEndCheck = 2, kEndMoments = 3 };
 // steps per launch an FP32 update moves about a fifth of the single-step
 // bytes), so the most steps per launch is a per-kind balance between the HBM
 // bytes saved, the halo nodes recomputed and the registers the delay lines
-// take (FP32: 62 / 67 / 82 / 95 VGPRs at 4 / 5 / 6 / 7 steps, and 24 KB of LDS
-// per block).  For the
+// take (FP32: 86 / 100 / 114 VGPRs at 4 / 5 / 6 steps, 96 and 24 KB of LDS per
+// block at 7).  For the
 // 16-bit kinds it also depends on how many of a launch's steps are rounded to
 // the storage type (FusedRounding): rounding every step, four steps per
 // launch were the fastest (FP16-SR 743, F16_SPLIT 819 us per launch on

@@ -104,8 +104,9 @@ Geometry geometry_of(const lbm_instance& in, int es, int layout, bool split = fa
 // whatever the number of stages; below five FP32 steps it is bound by memory
 // requests, above by VALU issue), so the way a short run is cut into launches
 // matters: 20 FP32 steps cost 3522 us as 7 + 7 + 6 and 4372 us as 5 + 5 + 5 +
-// 5.  (Check variants: 97 .. 128 VGPRs at four to seven FP32 steps, four waves
-// per SIMD, against five of the plain ones.)  The figures were taken with all
+// 5.  (Check variants: 114, 131, 143 and 159 VGPRs at four to seven FP32 steps,
+// four and then three waves per SIMD, against five or four of the plain ones.)
+// The figures were taken with all
 // delay lines in registers; only their ratios are used, and changing those of
 // the 16-bit kinds would change where their runs round.  16-bit kinds: rounding
 // every step (every_step) or only the last of a launch (FusedRounding).
