@@ -117,12 +117,13 @@ struct lbm3d_ctx {
     Layout3 L{};
     lbm3d_launch_shape shape{4, 1, 0, 1, 32};
     int fuse = 1;                // time steps per launch (1, or 2 with the z-marching kernel; see deep())
-    // two steps per launch when the z-marching tiles fill the chip (one block
-    // per CU): a launch takes about one tile's marching time, so small boxes
-    // run single steps (measured FP32 us per step, single / two: 64^3 5.3 /
-    // 37.1, 128^3 34.1 / 41.2 with 132 tiles, 192^3 137 / 124 with 384, 512^3
-    // 2670 / 1887; 512^3 FP16-SR 1464 / 1338, BF16-SR 1493 / 1378 with the
-    // window kept in 16 bits and column-and-row rounding words)
+    // two steps per launch when z-marching tiles of the shape's z range (32
+    // planes by default) fill the chip (one block per CU): a launch takes about
+    // one tile's marching time, so small boxes run single steps (measured FP32 us
+    // per step with that range, single / two: 64^3 5.3 / 37.1, 128^3 34.1 / 41.2
+    // with 132 tiles, 192^3 137 / 124 with 384, 512^3 2670 / 1887; 512^3 FP16-SR
+    // 1464 / 1338, BF16-SR 1493 / 1378 with the window kept in 16 bits and
+    // column-and-row rounding words).  z_range() may then take another range.
     void set_default_fuse() {
         const int64_t tiles = parts(cfg.nx, kPairW3) * parts(cfg.ny, kPairYO) * parts(cfg.nz, shape.zchunk);
         fuse = tiles >= kPairMinTiles ? 2 : 1;
@@ -136,18 +137,18 @@ struct lbm3d_ctx {
     // FP32 211 / 186; 192^3 99.8 / 77.2 (48) and 125 / 99.6; 130 x 500 x 300
     // 273 / 233 (150) and 389 / 353; 512^3 BF16 1309 / 1251 (57).  FP32 takes the
     // range only where the count falls clearly (fp32_percent), else 32 planes: in
-    // one round of blocks by 6%, in several by 9% (200 x 160 x 256, 29 planes in
-    // two rounds, 92% of the count: 139 / 145; 512^3, 57 planes, 95%: 1879 / 1938)
-    // and by 17% for ranges of more than 64 planes, where blocks on far ranges
-    // lose step with their neighbours: 23 boxes of 83 to 92% of the count ran in
-    // 0.885 to 1.093 of the time (531 x 498 x 240, 120 planes: 902 / 952; timings of
-    // one and the same kernel vary by up to a tenth between allocations of such
-    // boxes), 73 others within the limits in 0.91 on average.
+    // one round of blocks by 6%, in several by 9%, and there by 20% for ranges of
+    // more than 44 planes, where the blocks lose step with their neighbours.
+    // Measured in several rounds, both ranges in turn on one handle, time against 32
+    // planes: 27 boxes of up to 44 planes at 83 to 91% of the count 0.87 to 0.99
+    // and one 1.02, eight at 92 to 93% 0.93 to 1.05 (200 x 160 x 256, 29 planes: 139 /
+    // 145); 15 boxes of 45 to 64 planes 0.96 to 1.06 (512^3, 57 planes, 95%: 1879 /
+    // 1938) and 31 of more 0.93 to 1.11 (531 x 498 x 240, 120 planes: 902 / 952).
     struct Range {
         int planes;              // per block
         int64_t rounds, cost;    // rounds of kZBlocks blocks; plane times
     };
-    static int fp32_percent(const Range& r) { return r.rounds < 2 ? 94 : (r.planes > 64 ? 83 : 91); }
+    static int fp32_percent(const Range& r) { return r.rounds < 2 ? 94 : (r.planes > 44 ? 80 : 91); }
     // Columns of xo x yo nodes, `halo` extra planes per range, and the percentage
     // of the cost at 32 planes that a range has to stay below to replace it.  At
     // most kMostRanges ranges are tried: four full rounds of a single column, so

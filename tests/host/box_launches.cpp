@@ -79,7 +79,8 @@ static void planes() {
     for (const Case& c : {Case{301, 211, 163, LBM_BF16, 24}, Case{301, 211, 163, LBM_F32, 24}, Case{192, 192, 192, LBM_F32, 48},
                           Case{130, 500, 300, LBM_F32, 150}, Case{512, 512, 512, LBM_BF16, 57}, Case{512, 512, 512, LBM_F32, 32},
                           Case{200, 160, 256, LBM_F32, 32}, Case{200, 160, 256, LBM_F16, 29}, Case{531, 498, 240, LBM_F32, 32},
-                          Case{202, 436, 661, LBM_F32, 32}, Case{132, 526, 630, LBM_F32, 32}, Case{122, 213, 237, LBM_F32, 27}}) {
+                          Case{202, 436, 661, LBM_F32, 32}, Case{132, 526, 630, LBM_F32, 32}, Case{122, 213, 237, LBM_F32, 27},
+                          Case{319, 203, 378, LBM_F32, 32}, Case{720, 157, 521, LBM_F32, 32}}) {
         lbm3d_handle h = make(c.nx, c.ny, c.nz, c.storage);
         expect(lbm3d_set_step_fusion(h, 2) == LBM_OK, "step fusion");
         launches.clear();
